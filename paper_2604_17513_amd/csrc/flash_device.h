@@ -17,6 +17,7 @@ constexpr int kMaxGrip = 2;                       // grippers (bilateral attachm
 constexpr int kCacheSlots = kMaxObs + kMaxGrip;   // constraint rows per vertex: warm-start cache entries
 constexpr int kBlock = 256;
 constexpr int kBK = 16;         // panel width of the blocked factorisations in the contact solve
+__host__ __device__ constexpr int pad16(int n) { return (n + 15) & ~15; }   // leading dimensions of the dense kernels
 constexpr int kWsMaxFail = 3;   // learned-start failures after which an env keeps the plain start
 
 // Kernel classes for event timing (flash_kernel_name order).
@@ -31,7 +32,7 @@ struct DevBatch {
   int NV, NT;                 // total vertices / tets (tets: 4-node; tris: 3-node use the same arrays)
   int cap;                    // contact capacity per env
   int rmax;                   // capacity of the Woodbury capacitance system per env (3 rows per contact)
-  int rlds;                   // systems of up to rlds rows keep their LU panel in LDS, larger ones in lupan
+  int rlds;                   // rlds * (kBK + 2) values of LDS are the scratch of the dense kernels
   int max_newton;
   int lg_iterations;
   double h;
@@ -117,12 +118,9 @@ struct DevBatch {
   // contact-space scratch, in the contact-solve precision (double when csp64, else T)
   int csp64;                  // 1: the contact-space solve runs in FP64
   void* Gc;                   // [cap*cap per env] Gbar restricted to contacts
-  void* Ginv;                 // [cap*cap per env] inverse on the base set
-  void* Cm;                   // [rmax*rmax per env] capacitance matrix + row data
+  void* Ginv;                 // [pad16(cap)^2 per env] inverse on the base set
+  void* Cm;                   // [pad16(rmax)^2 per env] capacitance LU + row data
   int* base;                  // [cap per env] base-set contact ids (ordered)
-  void* scr;                  // [cap*16 per env] panel scratch of the blocked inverse
-  void* lupan;                // [rmax*(kBK+2) per env] LU panel (row stride kBK+1) and solve vector of
-                              // systems above rlds rows
   int* nbase;                 // [n_envs]
   int* lust;                  // [4 per env] stored capacitance factorisation: valid, rows, base version x2
 

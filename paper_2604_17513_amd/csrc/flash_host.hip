@@ -910,16 +910,14 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
   else B.cframe64 = B.csp64 ? dalloc<double>(9 * ne * cap, own) : nullptr;
   const size_t cts = B.csp64 ? sizeof(double) : sizeof(T);
   // contact-space matrices of the solves in LDS (none for the global-memory lightweight update)
-  const size_t csq = B.lite_global ? 1 : ne * cap * cap * cts;
-  B.Gc = dalloc<unsigned char>(csq, own);
-  B.Ginv = dalloc<unsigned char>(csq, own);
+  const size_t capp = pad16(B.cap);
+  B.Gc = dalloc<unsigned char>(B.lite_global ? 1 : ne * cap * cap * cts, own);
+  B.Ginv = dalloc<unsigned char>(B.lite_global ? 1 : ne * capp * capp * cts, own);
   {
-    const size_t rm = (size_t)B.rmax;
-    B.Cm = dalloc<unsigned char>(B.lite_global ? 1 : ne * (rm * rm + 16 * rm) * cts + 4 * ne * rm * sizeof(int), own);
-    B.lupan = dalloc<unsigned char>(B.lite_global ? 1 : ne * rm * (kBK + 2) * cts, own);
+    const size_t rm = (size_t)B.rmax, rmp = pad16(B.rmax);
+    B.Cm = dalloc<unsigned char>(B.lite_global ? 1 : ne * (rmp * rmp + 16 * rm) * cts + 3 * ne * rm * sizeof(int), own);
   }
   B.base = dalloc<int>(B.lite_global ? 1 : ne * cap, own);
-  B.scr = dalloc<unsigned char>(B.lite_global ? 1 : ne * cap * 16 * cts, own);
   B.lite_done = dalloc<int>(ne, own);
   HIPCHK(hipMemset(B.lite_done, 0, ne * sizeof(int)));
   B.lite_r = dalloc<unsigned long long>(B.lite_global ? (size_t)ne * B.lg_iterations * (B.max_newton + 1) : 1, own);

@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "flash_contact.h"
+#include "flash_dense.h"
 #include "flash_device.h"
 #include "flash_launch.h"
 
@@ -648,524 +649,6 @@ __global__ void __launch_bounds__(kBlock) k_gather(DevBatch<T> B) {
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-cooperative dense kernels for the contact solve.  Panels of kBK
-// columns; pivot blocks are staged in LDS; trailing updates use 4x4 register
-// tiles and read the panels from global memory (L1/L2 resident).
-// ---------------------------------------------------------------------------
-// kBK (panel width of the blocked factorisations) lives in flash_device.h
-
-// Runs use(k, load(k)) for k = k0, k0 + 1, ..., n - 1 in that order, with the loads of
-// BATCH consecutive terms issued before the first of them is used: under the contact
-// solve's register pressure the compiler otherwise waits for every load before issuing
-// the next (one global round trip per term).  The order of the uses, hence of any sums
-// they form, is unchanged.
-template <int BATCH, class LoadF, class UseF>
-__device__ __forceinline__ void batched_terms(int k0, int n, LoadF load, UseF use) {
-  using V = decltype(load(0));
-  typedef V vec __attribute__((ext_vector_type(BATCH)));   // a register value, never scratch
-  for (int kb = k0; kb < n; kb += BATCH) {
-    vec v = (V)0;
-#pragma unroll
-    for (int u = 0; u < BATCH; ++u)
-      if (kb + u < n) v[u] = load(kb + u);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < BATCH; ++u)
-      if (kb + u < n) use(kb + u, (V)v[u]);
-  }
-}
-
-// In-place inverse of a symmetric positive definite n x n matrix (ld n) by
-// blocked Gauss-Jordan sweeps.  CP: global scratch of n x kBK; P: LDS kBK x kBK;
-// v: LDS 2 * kBK.  lds (lds_cap values, or nullptr): when 2 kBK n values fit, the
-// panel column copy and the new row panel live there, so that the trailing update reads
-// memory only for the entries it updates.
-template <class T>
-__device__ __forceinline__ void wg_spd_inverse(T* M, int n, T* CP, T* P, T* v, T* lds, int lds_cap) {
-  const int tid = threadIdx.x;
-  const bool in_lds = lds && 2 * kBK * n <= lds_cap;
-  T* rp = in_lds ? lds + (size_t)kBK * n : nullptr;   // new row panel, rp[t * n + j]
-  if (in_lds) CP = lds;
-  for (int k0 = 0; k0 < n; k0 += kBK) {
-    const int kb = min(kBK, n - k0);
-    __syncthreads();
-    for (int idx = tid; idx < kb * kb; idx += kBlock) {
-      const int i = idx / kb, j = idx - i * kb;
-      P[i * kBK + j] = M[(size_t)(k0 + i) * n + k0 + j];
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // Gauss-Jordan on the pivot block by one wave (lane l owns rows l, l + 16 ... of column l % 16)
-      for (int k = 0; k < kb; ++k) {
-        const T piv = P[k * kBK + k];
-        const T colv = tid < kb ? P[tid * kBK + k] : T(0);
-        const T rowv = tid < kb ? P[k * kBK + tid] / piv : T(0);
-        __builtin_amdgcn_wave_barrier();
-        for (int idx = tid; idx < kb * kb; idx += 64) {
-          const int i = idx / kb, j = idx - i * kb;
-          const T ci = __shfl(colv, i, 64);
-          const T rj = __shfl(rowv, j, 64);
-          T val;
-          if (i == k) val = (j == k) ? T(1) / piv : rj;
-          else val = (j == k) ? -ci / piv : P[i * kBK + j] - ci * rj;
-          P[i * kBK + j] = val;
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    {
-      const int cnt = (n * kb - tid + kBlock - 1) / kBlock;   // this thread's elements
-      batched_terms<8>(0, cnt, [&](int k) {
-        const int idx = tid + k * kBlock, i = idx / kb, t = idx - i * kb;
-        return M[(size_t)i * n + k0 + t];
-      }, [&](int k, T v) {
-        const int idx = tid + k * kBlock, i = idx / kb, t = idx - i * kb;
-        CP[(size_t)i * kBK + t] = v;
-      });
-    }
-    __syncthreads();
-    // row panel: M[k0+t][j] <- sum_s Pinv[t][s] M[k0+s][j] for j outside the block
-    for (int j = tid; j < n; j += kBlock) {
-      if (j >= k0 && j < k0 + kb) continue;
-      T col[kBK];
-#pragma unroll
-      for (int s2 = 0; s2 < kBK; ++s2) col[s2] = s2 < kb ? M[(size_t)(k0 + s2) * n + j] : T(0);
-      __builtin_amdgcn_sched_barrier(0);
-      for (int t = 0; t < kb; ++t) {
-        T acc = 0;
-#pragma unroll
-        for (int s2 = 0; s2 < kBK; ++s2)
-          if (s2 < kb) acc += P[t * kBK + s2] * col[s2];
-        M[(size_t)(k0 + t) * n + j] = acc;
-        if (in_lds) rp[t * n + j] = acc;
-      }
-    }
-    if (in_lds)   // the block's own columns of the row panel enter only discarded products
-      for (int idx = tid; idx < kb * kb; idx += kBlock) rp[(idx / kb) * n + k0 + idx % kb] = T(0);
-    __syncthreads();
-    // trailing update M[i][j] -= sum_t M_old[i][k0+t] * M_new[k0+t][j]
-    const int nt = (n + 3) / 4;
-    if (in_lds) {
-      for (int tile = tid; tile < nt * nt; tile += kBlock) {
-        const int i0 = (tile / nt) * 4, j0 = (tile - (tile / nt) * nt) * 4;
-        T mv[4][4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int i = i0 + p, j = j0 + q;
-            const bool upd = i < n && j < n && !(i >= k0 && i < k0 + kb) && !(j >= k0 && j < k0 + kb);
-            mv[p][q] = upd ? M[(size_t)i * n + j] : T(0);
-          }
-        __builtin_amdgcn_sched_barrier(0);
-        T acc[4][4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[p][q] = 0;
-        for (int t = 0; t < kb; ++t) {
-          T a[4], r[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            a[q] = (i0 + q < n) ? CP[(size_t)(i0 + q) * kBK + t] : T(0);
-            r[q] = (j0 + q < n) ? rp[t * n + j0 + q] : T(0);
-          }
-#pragma unroll
-          for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[p][q] += a[p] * r[q];
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int i = i0 + p, j = j0 + q;
-            if (i < n && j < n && !(i >= k0 && i < k0 + kb) && !(j >= k0 && j < k0 + kb))
-              M[(size_t)i * n + j] = mv[p][q] - acc[p][q];
-          }
-      }
-    } else
-    for (int tile = tid; tile < nt * nt; tile += kBlock) {
-      const int i0 = (tile / nt) * 4, j0 = (tile - (tile / nt) * nt) * 4;
-      T acc[4][4];
-      for (int p = 0; p < 4; ++p)
-        for (int q = 0; q < 4; ++q) acc[p][q] = 0;
-      // panel columns and rows in batches of 8, every load of a batch issued before the products
-      for (int t0 = 0; t0 < kb; t0 += 8) {
-        T av[8][4], rv[8][4];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            av[u][q] = (t0 + u < kb && i0 + q < n) ? CP[(size_t)(i0 + q) * kBK + t0 + u] : T(0);
-            rv[u][q] = (t0 + u < kb && j0 + q < n) ? M[(size_t)(k0 + t0 + u) * n + j0 + q] : T(0);
-          }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (t0 + u < kb)
-            for (int p = 0; p < 4; ++p)
-              for (int q = 0; q < 4; ++q) acc[p][q] += av[u][p] * rv[u][q];
-      }
-      for (int p = 0; p < 4; ++p) {
-        const int i = i0 + p;
-        if (i >= n || (i >= k0 && i < k0 + kb)) continue;
-        for (int q = 0; q < 4; ++q) {
-          const int j = j0 + q;
-          if (j >= n || (j >= k0 && j < k0 + kb)) continue;
-          M[(size_t)i * n + j] -= acc[p][q];
-        }
-      }
-    }
-    // column panel: M[i][k0+t] <- -sum_s M_old[i][k0+s] Pinv[s][t]
-    for (int i = tid; i < n; i += kBlock) {
-      if (i >= k0 && i < k0 + kb) continue;
-      T cp[kBK];
-#pragma unroll
-      for (int s2 = 0; s2 < kBK; ++s2) cp[s2] = s2 < kb ? CP[(size_t)i * kBK + s2] : T(0);
-      __builtin_amdgcn_sched_barrier(0);
-      for (int t = 0; t < kb; ++t) {
-        T acc = 0;
-#pragma unroll
-        for (int s2 = 0; s2 < kBK; ++s2)
-          if (s2 < kb) acc += cp[s2] * P[s2 * kBK + t];
-        M[(size_t)i * n + k0 + t] = -acc;
-      }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < kb * kb; idx += kBlock) {
-      const int i = idx / kb, j = idx - i * kb;
-      M[(size_t)(k0 + i) * n + k0 + j] = P[i * kBK + j];
-    }
-  }
-  __syncthreads();
-}
-
-// Factors a general n x n matrix A (ld n, overwritten) by a blocked
-// right-looking LU with partial pivoting: rows are swapped across the whole
-// matrix (ties to the lowest row) and the pivot row of step k is stored in
-// piv[k].  Each kBK-column panel is factored in LDS (pan: n * (kBK + 1) values; with lds_cap > 0
-// values available from pan on, the panel's U12 block is kept beside it when it fits).
-template <class T>
-__device__ __forceinline__ void wg_lu_factor(T* A, int n, int* piv, int* perm, T* L11, T* pan, int lds_cap, double* sh_red,
-                                             int* sh_i, int* sh_piv) {
-  const int tid = threadIdx.x;
-  constexpr int PS = kBK + 1;   // odd panel row stride: column accesses spread over the LDS banks
-  __shared__ T sh_ui[kBK * kBK];
-  for (int k0 = 0; k0 < n; k0 += kBK) {
-    const int kb = min(kBK, n - k0);
-    const int pr_rows = n - k0;
-    __syncthreads();
-    {
-      const int cnt = (pr_rows * kb - tid + kBlock - 1) / kBlock;   // this thread's elements
-      batched_terms<8>(0, cnt, [&](int k) {
-        const int idx = tid + k * kBlock, i = idx / kb, t = idx - i * kb;
-        return A[(size_t)(k0 + i) * n + k0 + t];
-      }, [&](int k, T v) {
-        const int idx = tid + k * kBlock, i = idx / kb, t = idx - i * kb;
-        pan[i * PS + t] = v;
-      });
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // panel factorisation by one wave: lane l owns panel rows l, l + 64, ...
-      for (int t = 0; t < kb; ++t) {
-        double best = -1.0;
-        int bi = pr_rows;
-        for (int i = t + tid; i < pr_rows; i += 64) {
-          const double a = fabs((double)pan[i * PS + t]);
-          if (a > best) { best = a; bi = i; }
-        }
-        for (int d = 32; d > 0; d >>= 1) {
-          const double ob = __shfl_xor(best, d, 64);
-          const int oi = __shfl_xor(bi, d, 64);
-          if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-        }
-        const int pr = bi < pr_rows ? bi : t;
-        if (tid == 0) piv[k0 + t] = k0 + pr;
-        if (pr != t && tid < kb) {
-          const T t0 = pan[t * PS + tid];
-          pan[t * PS + tid] = pan[pr * PS + tid];
-          pan[pr * PS + tid] = t0;
-        }
-        __builtin_amdgcn_wave_barrier();
-        const T pv = pan[t * PS + t];
-        // the pivot row right of the diagonal, in registers (fixed-size loops, so that the array is
-        // never indexed dynamically and stays out of scratch)
-        T urow[kBK];
-#pragma unroll
-        for (int q = 0; q < kBK; ++q) urow[q] = (t + 1 + q < kb) ? pan[t * PS + t + 1 + q] : T(0);
-        for (int i = t + 1 + tid; i < pr_rows; i += 64) {
-          const T l = pv != T(0) ? pan[i * PS + t] / pv : T(0);
-          pan[i * PS + t] = l;
-#pragma unroll
-          for (int q = 0; q < kBK; ++q)
-            if (t + 1 + q < kb) pan[i * PS + t + 1 + q] -= l * urow[q];
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-    // The diagonal block is stored as the inverses of its factors (strictly lower part: the
-    // unit lower inverse, upper part: the upper inverse), so that every triangular solve with
-    // it (U12 below, wg_lu_apply) is a small matrix-vector product instead of a serial
-    // substitution.  Lane cc forms column cc of both inverses by substitution; a zero pivot
-    // gives a zero row (the solve then sets that unknown to zero).
-    if (tid < kb) {
-      const int cc = tid;
-      T* LI = L11;      // unit lower inverse, kept for U12
-      T* UI = sh_ui;
-      for (int i = 0; i < kb; ++i) {
-        T v = (i == cc) ? T(1) : T(0);
-        for (int s2 = 0; s2 < i; ++s2) v -= pan[i * PS + s2] * LI[s2 * kBK + cc];
-        LI[i * kBK + cc] = v;
-      }
-      for (int i = kb - 1; i >= 0; --i) {
-        T v = (i == cc) ? T(1) : T(0);
-        for (int s2 = i + 1; s2 < kb; ++s2) v -= pan[i * PS + s2] * UI[s2 * kBK + cc];
-        const T d = pan[i * PS + i];
-        UI[i * kBK + cc] = d != T(0) ? v / d : T(0);
-      }
-      for (int i = 0; i < kb; ++i)
-        A[(size_t)(k0 + i) * n + k0 + cc] = (cc < i) ? LI[i * kBK + cc] : UI[i * kBK + cc];
-    }
-    // write the rest of the factored panel back; apply the block's row swaps to the other columns
-    for (int idx = kb * kb + tid; idx < pr_rows * kb; idx += kBlock) {
-      const int i = idx / kb, t = idx - i * kb;
-      A[(size_t)(k0 + i) * n + k0 + t] = pan[i * PS + t];
-    }
-    for (int j = tid; j < n; j += kBlock) {
-      if (j >= k0 && j < k0 + kb) continue;
-      for (int t = 0; t < kb; ++t) {
-        const int pr = piv[k0 + t];
-        if (pr != k0 + t) {
-          const T t0 = A[(size_t)(k0 + t) * n + j];
-          A[(size_t)(k0 + t) * n + j] = A[(size_t)pr * n + j];
-          A[(size_t)pr * n + j] = t0;
-        }
-      }
-    }
-    __syncthreads();
-    // U12 = L11^-1 A12 with the unit lower inverse in L11 (rows taken last to first, so that
-    // col[s < t] still holds the input).  When it fits beside the panel in LDS (lds_cap values
-    // from pan on), U12 is also kept there for the trailing update.
-    const int m0 = k0 + kb, mm = n - m0;
-    T* u12 = pan + pr_rows * PS;
-    const bool u12_lds = lds_cap > 0 && pr_rows * PS + kb * mm <= lds_cap;
-    for (int j = k0 + kb + tid; j < n; j += kBlock) {
-      T col[kBK];
-      for (int t = 0; t < kb; ++t) col[t] = A[(size_t)(k0 + t) * n + j];
-      for (int t = kb - 1; t > 0; --t) {
-        T v = col[t];
-        for (int s2 = 0; s2 < t; ++s2) v += L11[t * kBK + s2] * col[s2];
-        col[t] = v;
-      }
-      for (int t = 0; t < kb; ++t) {
-        A[(size_t)(k0 + t) * n + j] = col[t];
-        if (u12_lds) u12[t * mm + (j - m0)] = col[t];
-      }
-    }
-    __syncthreads();
-    // A22 -= L21 U12 (L21 read from the LDS panel) in 4 x 4 tiles
-    if (mm > 0) {
-      const int nt = (mm + 3) / 4;
-      if (u12_lds) {
-        // both operands in LDS: the tile's 16 entries of A22 are loaded together before the
-        // products, one round trip per tile
-        auto tile_origin = [&](int tile, int& ti, int& tj) {
-          ti = m0 + (tile / nt) * 4;
-          tj = m0 + (tile - (tile / nt) * nt) * 4;
-        };
-        auto load_tile = [&](int ti, int tj, T (&v)[4][4]) {
-#pragma unroll
-          for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[p][q] = (ti + p < n && tj + q < n) ? A[(size_t)(ti + p) * n + tj + q] : T(0);
-        };
-        auto update_tile = [&](int ti, int tj, const T (&v)[4][4]) {
-          T acc[4][4];
-#pragma unroll
-          for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[p][q] = 0;
-          for (int t = 0; t < kb; ++t) {
-            T a[4], b[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              a[q] = (ti + q < n) ? pan[(ti + q - k0) * PS + t] : T(0);
-              b[q] = (tj + q < n) ? u12[t * mm + (tj + q - m0)] : T(0);
-            }
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-              for (int q = 0; q < 4; ++q) acc[p][q] += a[p] * b[q];
-          }
-#pragma unroll
-          for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (ti + p < n && tj + q < n) A[(size_t)(ti + p) * n + tj + q] = v[p][q] - acc[p][q];
-        };
-        for (int tile = tid; tile < nt * nt; tile += kBlock) {
-          int ti, tj;
-          tile_origin(tile, ti, tj);
-          T v[4][4];
-          load_tile(ti, tj, v);
-          __builtin_amdgcn_sched_barrier(0);
-          update_tile(ti, tj, v);
-        }
-      } else {
-        for (int tile = tid; tile < nt * nt; tile += kBlock) {
-          const int ti0 = m0 + (tile / nt) * 4, tj0 = m0 + (tile - (tile / nt) * nt) * 4;
-          T acc[4][4];
-          for (int p = 0; p < 4; ++p)
-            for (int q = 0; q < 4; ++q) acc[p][q] = 0;
-          // U12 rows in batches of 8, every load of a batch issued before the products
-          for (int t0 = 0; t0 < kb; t0 += 8) {
-            T bv[8][4];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                bv[u][q] = (t0 + u < kb && tj0 + q < n) ? A[(size_t)(k0 + t0 + u) * n + tj0 + q] : T(0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              if (t0 + u < kb) {
-                T a[4];
-                for (int q = 0; q < 4; ++q) a[q] = (ti0 + q < n) ? pan[(ti0 + q - k0) * PS + t0 + u] : T(0);
-                for (int p = 0; p < 4; ++p)
-                  for (int q = 0; q < 4; ++q) acc[p][q] += a[p] * bv[u][q];
-              }
-            }
-          }
-          for (int p = 0; p < 4; ++p) {
-            if (ti0 + p >= n) continue;
-            for (int q = 0; q < 4; ++q)
-              if (tj0 + q < n) A[(size_t)(ti0 + p) * n + tj0 + q] -= acc[p][q];
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  // the row swaps as one gather: applying them to the identity gives perm, so that
-  // (P y)[q] = y[perm[q]]; built in the panel scratch, then copied out in parallel
-  int* pw = reinterpret_cast<int*>(pan);
-  for (int q = tid; q < n; q += kBlock) pw[q] = q;
-  __syncthreads();
-  if (tid == 0)
-    for (int k = 0; k < n; ++k) {
-      const int pr = piv[k];
-      if (pr != k) { const int t0 = pw[k]; pw[k] = pw[pr]; pw[pr] = t0; }
-    }
-  __syncthreads();
-  for (int q = tid; q < n; q += kBlock) perm[q] = pw[q];
-  __syncthreads();
-}
-
-// Solves A y = r with the factors of wg_lu_factor.  r[16 q + 6] holds the
-// right-hand side; the solution goes to r[16 q + 7].  perm: the row gather of the
-// pivoting; ys: scratch of n values.  The diagonal blocks hold the inverses of their
-// factors, so each block step is a 16-lane matrix-vector product followed by the update
-// of the remaining rows.  dstage (LDS of 16 n values, or nullptr): the diagonal blocks are
-// first staged there in one pass, so that the sequential block steps read them from LDS.
-template <class T>
-__device__ __forceinline__ void wg_lu_apply(const T* A, int n, const int* perm, T* r, T* ys, T* dstage) {
-  const int tid = threadIdx.x;
-  const int nblk = (n + kBK - 1) / kBK;
-  __syncthreads();
-  for (int q = tid; q < n; q += kBlock) ys[q] = r[16 * perm[q] + 6];
-  if (dstage) {
-    const int cnt = (nblk * kBK * kBK - tid + kBlock - 1) / kBlock;   // this thread's entries
-    batched_terms<8>(0, cnt, [&](int k) {
-      const int idx = tid + k * kBlock, b = idx / (kBK * kBK), ii = (idx / kBK) % kBK, jj = idx % kBK;
-      const int k0 = b * kBK, kb = min(kBK, n - k0);
-      return (ii < kb && jj < kb) ? A[(size_t)(k0 + ii) * n + k0 + jj] : T(0);
-    }, [&](int k, T v) { dstage[tid + k * kBlock] = v; });
-  }
-  __syncthreads();
-  // diagonal-block row tid of block b (kb columns), from LDS or memory
-  auto drow = [&](int b, int k0) -> const T* {
-    return dstage ? dstage + (size_t)b * kBK * kBK + tid * kBK : A + (size_t)(k0 + tid) * n + k0;
-  };
-  // Each thread's first row of the next block step is loaded one step ahead (the loads do not
-  // depend on the solution), so that they complete under the current step's barriers; further
-  // rows of a thread (systems above kBlock + kBK rows) are loaded when used.
-  T pre[kBK];
-  auto prefetch = [&](int row, int k0n, int kbn) {
-#pragma unroll
-    for (int t = 0; t < kBK; ++t) pre[t] = (row < n && t < kbn) ? A[(size_t)row * n + k0n + t] : T(0);
-  };
-  // forward substitution with the unit lower factor
-  prefetch(min(kBK, n) + tid, 0, min(kBK, n));
-  for (int k0 = 0; k0 < n; k0 += kBK) {
-    const int kb = min(kBK, n - k0);
-    T v = 0;
-    if (tid < kb) {
-      const T* Ar = drow(k0 / kBK, k0);
-      v = ys[k0 + tid];
-      for (int s2 = 0; s2 < tid; ++s2) v += Ar[s2] * ys[k0 + s2];
-    }
-    __syncthreads();
-    if (tid < kb) ys[k0 + tid] = v;
-    __syncthreads();
-    {
-      const int i = k0 + kb + tid;
-      if (i < n) {
-        T acc = 0;
-#pragma unroll
-        for (int t = 0; t < kBK; ++t)
-          if (t < kb) acc += pre[t] * ys[k0 + t];
-        ys[i] -= acc;
-      }
-      const int k0n = k0 + kBK, kbn = min(kBK, n - k0n);
-      if (k0n < n) prefetch(k0n + kbn + tid, k0n, kbn);
-    }
-    for (int i = k0 + kb + kBlock + tid; i < n; i += kBlock) {
-      T acc = 0;
-      const T* Ar = A + (size_t)i * n + k0;
-      batched_terms<8>(0, kb, [&](int t) { return Ar[t]; }, [&](int t, T a) { acc += a * ys[k0 + t]; });
-      ys[i] -= acc;
-    }
-    __syncthreads();
-  }
-  // back substitution with the upper factor
-  if (nblk > 1) prefetch(tid < (nblk - 1) * kBK ? tid : n, (nblk - 1) * kBK, min(kBK, n - (nblk - 1) * kBK));
-  for (int bk = nblk - 1; bk >= 0; --bk) {
-    const int k0 = bk * kBK, kb = min(kBK, n - k0);
-    T v = 0;
-    if (tid < kb) {
-      const T* Ar = drow(bk, k0);
-      for (int s2 = tid; s2 < kb; ++s2) v += Ar[s2] * ys[k0 + s2];
-    }
-    __syncthreads();
-    if (tid < kb) ys[k0 + tid] = v;
-    __syncthreads();
-    {
-      const int i = tid;
-      if (i < k0) {
-        T acc = 0;
-#pragma unroll
-        for (int t = 0; t < kBK; ++t)
-          if (t < kb) acc += pre[t] * ys[k0 + t];
-        ys[i] -= acc;
-      }
-      if (bk > 0) prefetch(tid < k0 - kBK ? tid : n, k0 - kBK, kBK);
-    }
-    for (int i = kBlock + tid; i < k0; i += kBlock) {
-      T acc = 0;
-      const T* Ar = A + (size_t)i * n + k0;
-      batched_terms<8>(0, kb, [&](int t) { return Ar[t]; }, [&](int t, T a) { acc += a * ys[k0 + t]; });
-      ys[i] -= acc;
-    }
-    __syncthreads();
-  }
-  for (int q = tid; q < n; q += kBlock) r[16 * q + 7] = ys[q];
-  __syncthreads();
-}
-
-// ---------------------------------------------------------------------------
 // Contact subproblem (Eq. 2b with Eq. 4 at fixed projections): find lambda
 // with Phi(lambda) = 0 for Y(lambda) = y_free + W lambda,
 // W = h^2 F^T (Gc (x) I3) F the exact Delassus operator of the env.
@@ -1180,7 +663,7 @@ struct CspSmem {
   double* lam;                                 // [3*cap] multipliers, FP64
   T *Y, *dl, *Wd, *rv, *x0, *fw, *ph, *tmp;    // [3*cap]
   T *sp, *kap, *yh0, *yh1;                    // [cap]
-  T *pan, *ys;                                // [rlds*(kBK+1)], [rlds]
+  T* pan;                                     // [rlds*(kBK+2)] scratch of the dense kernels
   int *cls, *pos, *bas;                       // [cap]
 };
 
@@ -1344,20 +827,20 @@ __device__ __forceinline__ void csp_env(const DevBatch<T>& B, const T* mu_env, i
     S.Wd = p; p += 3 * cap; S.rv = p; p += 3 * cap; S.x0 = p; p += 3 * cap; S.fw = p; p += 3 * cap;
     S.ph = p; p += 3 * cap; S.tmp = p; p += 3 * cap;
     S.sp = p; p += cap; S.kap = p; p += cap; S.yh0 = p; p += cap; S.yh1 = p; p += cap;
-    S.pan = p; p += (size_t)B.rlds * (kBK + 1); S.ys = p; p += B.rlds;
+    S.pan = p; p += (size_t)B.rlds * (kBK + 2);
     int* ip = reinterpret_cast<int*>(p);
     S.cls = ip; ip += cap; S.pos = ip; ip += cap; S.bas = ip; ip += cap;
   }
   __shared__ double sh_red[kBlock / 64];
   __shared__ int sh_i[kBlock / 64];
-  __shared__ int sh_nb, sh_nR, sh_piv;
-  __shared__ CT sh_blk[kBK * kBK];
-  __shared__ CT sh_vv[2 * kBK];
+  __shared__ int sh_nb, sh_nR;
+  __shared__ DenseSmem<CT> sh_dense;
 
   const size_t cb = (size_t)e * cap;
   const CT* Gc = static_cast<const CT*>(B.Gc) + cb * cap;   // ld c
-  CT* Ginv = static_cast<CT*>(B.Ginv) + cb * cap;            // ld nb
-  CT* Cm = static_cast<CT*>(B.Cm) + (size_t)e * B.rmax * B.rmax;
+  const size_t capp = pad16(cap), rmp = pad16(B.rmax);
+  CT* Ginv = static_cast<CT*>(B.Ginv) + (size_t)e * capp * capp;   // ld pad16(nb)
+  CT* Cm = static_cast<CT*>(B.Cm) + (size_t)e * rmp * rmp;         // ld pad16(nR)
   const int v0 = B.voff[e];
   const CT hh = (CT)(B.h * B.h), ihh = CT(1) / hh;
   const CT mu = mu_env[e];
@@ -1380,14 +863,14 @@ __device__ __forceinline__ void csp_env(const DevBatch<T>& B, const T* mu_env, i
     }
   };
 
-  // per-R-row data in global scratch (after the rmax*rmax matrices):
+  // per-R-row data in global scratch (after the matrices):
   // vR(3) uR(3) rhs y Krow(3) Erow(3) -- 16 values per row
-  CT* Rv = static_cast<CT*>(B.Cm) + (size_t)B.n_envs * B.rmax * B.rmax + (size_t)e * B.rmax * 16;
-  int* Rj = reinterpret_cast<int*>(static_cast<CT*>(B.Cm) + (size_t)B.n_envs * B.rmax * B.rmax + (size_t)B.n_envs * B.rmax * 16) +
-            (size_t)e * B.rmax * 4;
+  CT* Rv = static_cast<CT*>(B.Cm) + (size_t)B.n_envs * rmp * rmp + (size_t)e * B.rmax * 16;
+  int* Rj = reinterpret_cast<int*>(static_cast<CT*>(B.Cm) + (size_t)B.n_envs * rmp * rmp + (size_t)B.n_envs * B.rmax * 16) +
+            (size_t)e * B.rmax * 3;
   int* RjF = Rj + B.rmax;      // row list of the stored factorisation
-  int* piv = Rj + 2 * B.rmax;  // its pivots
-  int* perm = Rj + 3 * B.rmax; // and the equivalent row gather
+  int* perm = Rj + 2 * B.rmax; // and the row of each of its positions
+  const int pan_cap = B.rlds * (kBK + 2);
   int* lust = B.lust + 4 * e;  // valid, nR, base version at factorisation, current base version
 
   // ---- load state ----
@@ -1605,19 +1088,24 @@ restart:
         __syncthreads();
       }
       nb = sh_nb;
-      // Ginv = inverse of Gc[base, base] (+1e-4 relative on repeated vertices), Gauss-Jordan
+      // Ginv = inverse of Gc[base, base] (+1e-4 relative on repeated vertices)
       {
-        const int cnt = (nb * nb - tid + kBlock - 1) / kBlock;   // this thread's entries
-        batched_terms<8>(0, cnt, [&](int k) {
-          const int idx = tid + k * kBlock, p = idx / nb, q = idx - p * nb;
-          return Gc[(size_t)S.bas[p] * c + S.bas[q]];
-        }, [&](int k, CT g) {
-          const int idx = tid + k * kBlock, p = idx / nb, q = idx - p * nb;
-          if (p == q && p > 0 && B.cvert[cb + S.bas[p]] == B.cvert[cb + S.bas[p - 1]]) g *= CT(1.0001);
-          Ginv[idx] = g;
-        });
+        // a wave takes every fourth row, a lane every 64th column; the padding holds the identity
+        const int ldb = pad16(nb);
+#pragma unroll 1
+        for (int q = lane_id(); q < ldb; q += 64) {
+          const int bq = S.bas[min(q, nb - 1)];
+          batched_terms<8>(0, ldb / (kBlock / 64), [&](int k) {
+            const int p = wave_id() + (kBlock / 64) * k;
+            return Gc[(size_t)S.bas[min(p, nb - 1)] * c + bq];
+          }, [&](int k, CT g) {
+            const int p = wave_id() + (kBlock / 64) * k;
+            if (p == q && p > 0 && p < nb && B.cvert[cb + S.bas[p]] == B.cvert[cb + S.bas[p - 1]]) g *= CT(1.0001);
+            Ginv[(size_t)p * ldb + q] = (p < nb && q < nb) ? g : (p == q ? CT(1) : CT(0));
+          });
+        }
       }
-      wg_spd_inverse(Ginv, nb, static_cast<CT*>(B.scr) + cb * kBK, sh_blk, sh_vv, S.pan, B.rlds * (kBK + 2));
+      wg_spd_inverse<CT>(Ginv, nb, (lds_ptr<CT>)S.pan, pan_cap, sh_dense);
       if (tid == 0) lust[3] += 1;
       __syncthreads();
       ++nref;
@@ -1656,6 +1144,7 @@ restart:
     __syncthreads();
 
     mark(3);
+    const int ldb = pad16(nb);
     // ---- capacitance rows R: base rows whose (K, E) differ from (I, 0) ----
     if (tid == 0) sh_nR = 0;
     __syncthreads();
@@ -1688,9 +1177,7 @@ restart:
     }
     const int nR = min(sh_nR, B.rmax);
     if (sh_nR > B.rmax && tid == 0) B.flags[e] |= 8;   // capacity exceeded: inexact direction
-    // LU panel and solve vector: LDS for systems up to rlds rows, global scratch above
-    CT* gpan = static_cast<CT*>(B.lupan) + (size_t)e * B.rmax * (kBK + 2);
-    CT* gys = gpan + (size_t)B.rmax * (kBK + 1);
+    // the rows' data is staged in LDS for the build while it fits
     const bool big = nR > B.rlds;
     bool reused = false;
     if (nR > 0) {
@@ -1735,34 +1222,48 @@ restart:
           // each entry reads memory once (its Ginv gather, batched)
           const CT* sv = S.pan;
           const int* si = reinterpret_cast<const int*>(S.pan + 9 * nR);
-          const int cnt = (nR * nR - tid + kBlock - 1) / kBlock;   // this thread's entries
-          batched_terms<8>(0, cnt, [&](int k) {
-            const int idx = tid + k * kBlock, q = idx / nR, s2 = idx - q * nR;
-            return Ginv[(size_t)si[3 * q + 2] * nb + si[3 * s2 + 2]];
-          }, [&](int k, CT g) {
-            const int idx = tid + k * kBlock, q = idx / nR, s2 = idx - q * nR;
-            const CT* vq = sv + 9 * q;
-            const CT* us = sv + 9 * s2 + 3;
-            CT v = ihh * g * (vq[0] * us[0] + vq[1] * us[1] + vq[2] * us[2]);
-            if (si[3 * q] == si[3 * s2]) v += vq[6 + si[3 * s2 + 1]];
-            Cm[idx] = v;
-          });
-        } else {
-          for (int idx = tid; idx < nR * nR; idx += kBlock) {
-            const int q = idx / nR, s2 = idx - q * nR;
-            const int jaq = Rj[q], jas = Rj[s2];
-            const int jq = jaq / 3, js = jas / 3, as = jas - 3 * js;
-            const CT* vq = Rv + 16 * q;
-            const CT* us = Rv + 16 * s2 + 3;
-            CT v = ihh * Ginv[(size_t)S.pos[jq] * nb + S.pos[js]] * (vq[0] * us[0] + vq[1] * us[1] + vq[2] * us[2]);
-            if (jq == js) v += vq[8 + as];
-            Cm[idx] = v;
+          const int ldc = pad16(nR);
+#pragma unroll 1
+          for (int s2 = lane_id(); s2 < ldc; s2 += 64) {
+            const int sc = min(s2, nR - 1);
+            const CT* us = sv + 9 * sc + 3;
+            const int js = si[3 * sc], as = si[3 * sc + 1], ps = si[3 * sc + 2];
+            batched_terms<8>(0, ldc / (kBlock / 64), [&](int k) {
+              const int q = min(wave_id() + (kBlock / 64) * k, nR - 1);
+              return Ginv[(size_t)si[3 * q + 2] * ldb + ps];
+            }, [&](int k, CT g) {
+              const int qr = wave_id() + (kBlock / 64) * k, q = min(qr, nR - 1);
+              const CT* vq = sv + 9 * q;
+              CT v = ihh * g * (vq[0] * us[0] + vq[1] * us[1] + vq[2] * us[2]);
+              if (si[3 * q] == js) v += vq[6 + as];
+              Cm[(size_t)qr * ldc + s2] = (qr < nR && s2 < nR) ? v : CT(0);
+            });
           }
+        } else {
+          const int ldc = pad16(nR);
+#pragma unroll 1
+          for (int s2 = lane_id(); s2 < ldc; s2 += 64)
+#pragma unroll 1
+            for (int q = wave_id(); q < ldc; q += kBlock / 64) {
+              CT v = 0;
+              if (q < nR && s2 < nR) {
+                const int jaq = Rj[q], jas = Rj[s2];
+                const int jq = jaq / 3, js = jas / 3, as = jas - 3 * js;
+                const CT* vq = Rv + 16 * q;
+                const CT* us = Rv + 16 * s2 + 3;
+                v = ihh * Ginv[(size_t)S.pos[jq] * ldb + S.pos[js]] * (vq[0] * us[0] + vq[1] * us[1] + vq[2] * us[2]);
+                if (jq == js) v += vq[8 + as];
+              }
+              Cm[(size_t)q * ldc + s2] = v;
+            }
         }
         __syncthreads();
         mark(4);
-        if (big) wg_lu_factor(Cm, nR, piv, perm, sh_blk, gpan, 0, sh_red, sh_i, &sh_piv);
-        else wg_lu_factor(Cm, nR, piv, perm, sh_blk, S.pan, B.rlds * (kBK + 2), sh_red, sh_i, &sh_piv);
+        {
+          const lds_ptr<int> lp = wg_lu_factor<CT>(Cm, nR, (lds_ptr<CT>)S.pan, pan_cap, sh_dense);
+          for (int q = tid; q < nR; q += kBlock) perm[q] = lp[q];
+          __syncthreads();
+        }
         if (tid == 0) { lust[0] = 1; lust[1] = nR; lust[2] = lust[3]; ++nfact; sum_nr += nR; max_nr = max(max_nr, nR); }
       } else if (tid == 0) {
         ++nreuse;
@@ -1781,7 +1282,7 @@ restart:
       __syncthreads();
       for (int p = tid; p < nb; p += kBlock) {
         CT w0 = 0, w1 = 0, w2 = 0;
-        batched_terms<16>(0, nb, [&](int q) { return Ginv[(size_t)q * nb + p]; }, [&](int q, CT g) {
+        batched_terms<16>(0, nb, [&](int q) { return Ginv[(size_t)q * ldb + p]; }, [&](int q, CT g) {
           w0 += g * S.fw[3 * q]; w1 += g * S.fw[3 * q + 1]; w2 += g * S.fw[3 * q + 2];
         });
         const int j = S.bas[p];
@@ -1790,56 +1291,35 @@ restart:
       }
       __syncthreads();
       if (nR > 0) {
+        // the row right-hand sides and their solution live in fw (free once x0 is formed)
         for (int q = tid; q < nR; q += kBlock) {
           const int ja = Rj[q], j = ja / 3, a = ja - 3 * (ja / 3);
-          CT* rv = Rv + 16 * q;
+          const CT* rv = Rv + 16 * q;
           CT rr = -rin[3 * j + a];
           for (int b = 0; b < 3; ++b) rr += rv[8 + b] * rin[3 * j + b] + rv[11 + b] * S.x0[3 * j + b];
-          rv[6] = rr;
+          S.fw[q] = rr;
         }
-        if (big) wg_lu_apply(Cm, nR, perm, Rv, gys, static_cast<CT*>(nullptr));
-        else {
-          // the LDS panel (rlds (kBK + 1) values) is free during the solve; it holds the staged
-          // diagonal blocks unless the system is too small for a whole block to fit
-          const bool fits = ((nR + kBK - 1) / kBK) * kBK * kBK <= B.rlds * (kBK + 1);
-          wg_lu_apply(Cm, nR, perm, Rv, S.ys, fits ? S.pan : static_cast<CT*>(nullptr));
+        wg_lu_apply<CT>(Cm, nR, perm, (lds_ptr<CT>)S.fw, (lds_ptr<CT>)S.pan, (lds_ptr<int>)(S.pan + pad16(nR)));
+        // the rows' vectors y_s u_s and base positions staged in the (free) LDS panel, so that only the
+        // Ginv gathers go to memory
+        CT* st = S.pan;
+        int* spos = reinterpret_cast<int*>(S.pan + 4 * nR);
+        for (int q = tid; q < nR; q += kBlock) {
+          const CT* rv = Rv + 16 * q;
+          st[4 * q] = S.fw[q]; st[4 * q + 1] = rv[3]; st[4 * q + 2] = rv[4]; st[4 * q + 3] = rv[5];
+          spos[q] = S.pos[Rj[q] / 3];
         }
-        if (!big) {
-          // the rows' solution y_s, vectors u_s and base positions staged in the (now free)
-          // LDS panel and solve vector, so that only the Ginv gathers go to memory
-          CT* st = S.pan;
-          int* spos = reinterpret_cast<int*>(S.ys);
-          for (int q = tid; q < nR; q += kBlock) {
-            const CT* rv = Rv + 16 * q;
-            st[4 * q] = rv[7]; st[4 * q + 1] = rv[3]; st[4 * q + 2] = rv[4]; st[4 * q + 3] = rv[5];
-            spos[q] = S.pos[Rj[q] / 3];
-          }
-          __syncthreads();
-          for (int p = tid; p < nb; p += kBlock) {
-            CT w0 = 0, w1 = 0, w2 = 0;
-            batched_terms<16>(0, nR, [&](int s2) { return Ginv[(size_t)spos[s2] * nb + p]; }, [&](int s2, CT gi) {
-              const CT g = gi * st[4 * s2];
-              w0 += g * st[4 * s2 + 1]; w1 += g * st[4 * s2 + 2]; w2 += g * st[4 * s2 + 3];
-            });
-            const int j = S.bas[p];
-            const CT* F = Fr + 9 * j;
-            for (int a = 0; a < 3; ++a)
-              dout[3 * j + a] = S.x0[3 * j + a] - ihh * (F[3 * a] * w0 + F[3 * a + 1] * w1 + F[3 * a + 2] * w2);
-          }
-        } else {
-          for (int p = tid; p < nb; p += kBlock) {
-            CT w0 = 0, w1 = 0, w2 = 0;
-            for (int s2 = 0; s2 < nR; ++s2) {
-              const int js = Rj[s2] / 3;
-              const CT g = Ginv[(size_t)S.pos[js] * nb + p] * Rv[16 * s2 + 7];
-              const CT* us = Rv + 16 * s2 + 3;
-              w0 += g * us[0]; w1 += g * us[1]; w2 += g * us[2];
-            }
-            const int j = S.bas[p];
-            const CT* F = Fr + 9 * j;
-            for (int a = 0; a < 3; ++a)
-              dout[3 * j + a] = S.x0[3 * j + a] - ihh * (F[3 * a] * w0 + F[3 * a + 1] * w1 + F[3 * a + 2] * w2);
-          }
+        __syncthreads();
+        for (int p = tid; p < nb; p += kBlock) {
+          CT w0 = 0, w1 = 0, w2 = 0;
+          batched_terms<16>(0, nR, [&](int s2) { return Ginv[(size_t)spos[s2] * ldb + p]; }, [&](int s2, CT gi) {
+            const CT g = gi * st[4 * s2];
+            w0 += g * st[4 * s2 + 1]; w1 += g * st[4 * s2 + 2]; w2 += g * st[4 * s2 + 3];
+          });
+          const int j = S.bas[p];
+          const CT* F = Fr + 9 * j;
+          for (int a = 0; a < 3; ++a)
+            dout[3 * j + a] = S.x0[3 * j + a] - ihh * (F[3 * a] * w0 + F[3 * a + 1] * w1 + F[3 * a + 2] * w2);
         }
       } else {
         for (int p = tid; p < nb; p += kBlock) {

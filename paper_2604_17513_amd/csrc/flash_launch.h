@@ -83,10 +83,10 @@ template <class T> void launch_lg_fused(const DevBatch<T>& B, const T* mu_env, h
 // one contact solve factors, and the rows of its LU panel staged in LDS.
 inline int csp_capacity(int requested) { return requested > 0 ? requested : 320; }
 inline int csp_rows(int cap) { return 3 * cap < 1536 ? 3 * cap : 1536; }
-inline int csp_lds_rows(int rmax) { return rmax < 480 ? rmax : 480; }
+inline int csp_lds_rows(int rmax) { return rmax < 48 ? 48 : rmax < 480 ? rmax : 480; }
 // Dynamic LDS of one contact solve in its precision CT: FP64 multipliers (3 per contact), the
-// per-contact frames, Jacobian and E blocks (28 values), the staged LU panel (rlds rows of
-// kBK + 2), contact indices (3 per contact) and a 64-value reduction area.
+// per-contact frames, Jacobian and E blocks (28 values), the scratch of the dense kernels (rlds rows of
+// kBK + 2 values), contact indices (3 per contact) and a 64-value reduction area.
 template <class CT>
 __host__ __device__ constexpr size_t csp_smem_bytes(int cap, int rlds) {
   return (size_t)cap * 3 * sizeof(double) + (size_t)cap * (24 + 4) * sizeof(CT) + (size_t)rlds * (kBK + 2) * sizeof(CT) +
