@@ -154,67 +154,118 @@ struct FusedSmem {
   __bf16 w2[kHidden * kLdH];
   __bf16 w3[kHidden * kLdH];
   __bf16 w4[kOut * kLdH];
-  float b[3 * kHidden + 4];
+  alignas(16) float b[3 * kHidden + 4];
   float nrm[2 * kFeat];
 };
 constexpr size_t kFusedSmem = sizeof(FusedSmem);
 
 __device__ __forceinline__ int perm16(int c) { return (c & ~12) | ((c & 4) << 1) | ((c & 8) >> 1); }
 
-__device__ __forceinline__ __bf16 to_bf(float f) { return __builtin_bit_cast(__bf16, f2bf(f)); }
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-// one hidden layer: hn = relu(W h + b) on the 4 x 16 register tile of a wave
-__device__ __forceinline__ void fused_hidden(const __bf16* w, const float* bias, const float (&h)[4][16],
-                                             float (&hn)[4][16], int l) {
-  bf16x8 bop[4][2];
-  for (int mt = 0; mt < 4; ++mt)
-    for (int p = 0; p < 2; ++p)
-      for (int t = 0; t < 8; ++t) bop[mt][p][t] = to_bf(h[mt][8 * p + t]);
-  for (int mt = 0; mt < 4; ++mt) {
-    const __bf16* wrow = w + (32 * mt + (l & 31)) * kLdH + 8 * (l >> 5);
-    floatx16 acc = {};
-    for (int q = 0; q < 4; ++q)
-      for (int p = 0; p < 2; ++p) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop[q][p], acc, 0, 0, 0);
-      }
-    for (int r = 0; r < 16; ++r)
-      hn[mt][r] = fmaxf(acc[r] + bias[32 * mt + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)], 0.f);
+// Two floats to bf16 (nearest even) in one instruction.
+__device__ __forceinline__ bf16x2 to_bf2(float a, float b) {
+  const floatx2 v = {a, b};
+  return __builtin_convertvector(v, bf16x2);
+}
+
+// Rounded weights [rows x cols] (row-major floats at W, 16-byte groups) to LDS rows of stride ld, columns
+// permuted by perm16 with PERM: each group of 4 columns stays together.  U groups per thread in flight.
+template <bool PERM, int U>
+__device__ __forceinline__ void stage_weights(const float* W, int rows, int cols, __bf16* dst, int ld) {
+  const int n4 = rows * cols / 4;
+  for (int i0 = threadIdx.x; i0 < n4; i0 += U * blockDim.x) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float* src = W + 4 * (size_t)min(i0 + u * (int)blockDim.x, n4 - 1);
+      v[u] = make_float4(src[0], src[1], src[2], src[3]);   // the caller's weights may be 4-byte aligned only
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * (int)blockDim.x;
+      if (i >= n4) continue;
+      const int r = 4 * i / cols, c = 4 * i - r * cols;
+      bf16x2* d = reinterpret_cast<bf16x2*>(dst + r * ld + (PERM ? perm16(c) : c));
+      d[0] = to_bf2(v[u].x, v[u].y);
+      d[1] = to_bf2(v[u].z, v[u].w);
+    }
   }
 }
 
-__device__ __forceinline__ void fused_store(float* H, long row, long rows, const float (&h)[4][16], int l) {
-  if (row >= rows) return;
-  for (int mt = 0; mt < 4; ++mt)
-    for (int q = 0; q < 4; ++q) {
-      float4 v = make_float4(h[mt][4 * q], h[mt][4 * q + 1], h[mt][4 * q + 2], h[mt][4 * q + 3]);
-      *reinterpret_cast<float4*>(H + row * kHidden + 32 * mt + 8 * q + 4 * (l >> 5)) = v;
+// Tiles (of 32 rows) a wave takes together: they share every A operand read from LDS.
+constexpr int kPair = 2;
+
+// Bias, ReLU and rounding of one 32-neuron output tile mt: the next layer's operands (and with H the
+// activations of row `row`, when it is below rows).
+__device__ __forceinline__ void hidden_epilogue(const floatx16& acc, const float* bias, int mt, int l, bf16x8 (&out)[2],
+                                                float* H, long row, long rows) {
+  float v[16];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 b = *reinterpret_cast<const float4*>(bias + 32 * mt + 8 * q + 4 * (l >> 5));
+    v[4 * q] = fmaxf(acc[4 * q] + b.x, 0.f);
+    v[4 * q + 1] = fmaxf(acc[4 * q + 1] + b.y, 0.f);
+    v[4 * q + 2] = fmaxf(acc[4 * q + 2] + b.z, 0.f);
+    v[4 * q + 3] = fmaxf(acc[4 * q + 3] + b.w, 0.f);
+  }
+  if (H && row < rows) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(H + row * kHidden + 32 * mt + 8 * q + 4 * (l >> 5)) =
+          make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const bf16x2 c = to_bf2(v[8 * p + 2 * t], v[8 * p + 2 * t + 1]);
+      out[p][2 * t] = c[0];
+      out[p][2 * t + 1] = c[1];
     }
+}
+
+// One hidden layer of a wave's kPair tiles: out = relu(W in + b), in and out as operands.
+__device__ __forceinline__ void fused_hidden(const __bf16* w, const float* bias, const bf16x8 (&in)[kPair][4][2],
+                                             bf16x8 (&out)[kPair][4][2], int l, float* H, const long (&row)[kPair],
+                                             long rows) {
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const __bf16* wrow = w + (32 * mt + (l & 31)) * kLdH + 8 * (l >> 5);
+    floatx16 acc[kPair] = {};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
+#pragma unroll
+        for (int g = 0; g < kPair; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, in[g][q][p], acc[g], 0, 0, 0);
+      }
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) hidden_epilogue(acc[g], bias, mt, l, out[g][mt], H, row[g], rows);
+  }
 }
 
 // Y = network(X) for `rows` rows.  norm != nullptr: X holds raw features, normalised on load.
 // need != nullptr: 32-row tiles without a flagged row are skipped (their Y is left as is).
-// H1 != nullptr: the hidden activations are stored for the backward pass.
-__global__ void __launch_bounds__(64 * kWaves) k_mlp_fused(const float* W, const float* norm, const float* X,
-                                                           long rows, const int* need, float* Y, float* H1,
-                                                           float* H2, float* H3) {
+// STORE: the hidden activations go to H1, H2, H3 for the backward pass.
+// What bounds it: the matrix cores (76 MFMA of 32 cycles per tile) against about 500 vector instructions of
+// bias, ReLU and rounding; two tiles per wave share the weights' LDS reads and hide each other's chains,
+// and rounding takes half an instruction per value (v_cvt_pk_bf16_f32) instead of six.  One million rows:
+// 81 us a call (0.91 PFLOP/s of network arithmetic), 277 us with one tile per wave and rounding in integer code.
+template <bool STORE>
+__global__ void __launch_bounds__(64 * kWaves, 2) k_mlp_fused(const float* W, const float* norm, const float* X,
+                                                              long rows, const int* need, float* Y, float* H1,
+                                                              float* H2, float* H3) {
   extern __shared__ __align__(16) unsigned char fsm_raw[];
   FusedSmem& S = *reinterpret_cast<FusedSmem*>(fsm_raw);
   const MlpLayout L;
   const int tid = threadIdx.x;
-  for (int i = tid; i < kHidden * kFeat; i += blockDim.x) {
-    const int r = i / kFeat, c = i - r * kFeat;
-    S.w1[r * kLd1 + c] = to_bf(W[L.w1 + i]);
-  }
-  for (int i = tid; i < kHidden * kHidden; i += blockDim.x) {
-    const int r = i / kHidden, c = i - r * kHidden;
-    S.w2[r * kLdH + perm16(c)] = to_bf(W[L.w2 + i]);
-    S.w3[r * kLdH + perm16(c)] = to_bf(W[L.w3 + i]);
-  }
-  for (int i = tid; i < kOut * kHidden; i += blockDim.x) {
-    const int r = i / kHidden, c = i - r * kHidden;
-    S.w4[r * kLdH + perm16(c)] = to_bf(W[L.w4 + i]);
-  }
+  stage_weights<true, 8>(W + L.w2, kHidden, kHidden, S.w2, kLdH);
+  stage_weights<true, 8>(W + L.w3, kHidden, kHidden, S.w3, kLdH);
+  stage_weights<false, 2>(W + L.w1, kHidden, kFeat, S.w1, kLd1);
+  stage_weights<true, 1>(W + L.w4, kOut, kHidden, S.w4, kLdH);
   for (int i = tid; i < kHidden; i += blockDim.x) {
     S.b[i] = W[L.b1 + i];
     S.b[kHidden + i] = W[L.b2 + i];
@@ -226,62 +277,81 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_fused(const float* W, const
 
   const int l = tid & 63, wave = tid >> 6;
   const int h = l >> 5;
-  const long ntiles = (rows + 31) / 32;
-  for (long tile = (long)blockIdx.x * kWaves + wave; tile < ntiles; tile += (long)gridDim.x * kWaves) {
-    const long row = tile * 32 + (l & 31);
-    if (need) {
-      const bool mine = row < rows && need[row] != 0;
-      if (__ballot(mine) == 0) continue;
+  const long npairs = ((rows + 31) / 32 + kPair - 1) / kPair;
+  for (long pair = (long)blockIdx.x * kWaves + wave; pair < npairs; pair += (long)gridDim.x * kWaves) {
+    long row[kPair];
+    bool on[kPair];
+    bool any = false;
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) {
+      row[g] = (pair * kPair + g) * 32 + (l & 31);
+      on[g] = true;
+      if (need) on[g] = __ballot(row[g] < rows && need[row[g]] != 0) != 0;
+      any |= on[g];
     }
-    // layer 1: B operand = 8 features of this lane's sample
-    bf16x8 xb;
-    for (int t = 0; t < 8; ++t) {
-      const int k = 8 * h + t;
-      const float v = row < rows ? X[row * kFeat + k] : 0.f;
-      xb[t] = to_bf((v - S.nrm[k]) * S.nrm[kFeat + k]);
+    if (!any) continue;
+    // layer 1: B operand = 8 features of this lane's sample (rows past the end repeat the last one, unused)
+    bf16x8 xb[kPair];
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) {
+      const float* x = X + (row[g] < rows ? row[g] : rows - 1) * kFeat + 8 * h;
+      float v[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = x[t];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = (v[t] - S.nrm[8 * h + t]) * S.nrm[kFeat + 8 * h + t];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const bf16x2 c = to_bf2(v[2 * t], v[2 * t + 1]);
+        xb[g][2 * t] = c[0];
+        xb[g][2 * t + 1] = c[1];
+      }
     }
-    float ha[4][16], hb[4][16];
+    bf16x8 ha[kPair][4][2], hb[kPair][4][2];
+#pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       const bf16x8 a = *reinterpret_cast<const bf16x8*>(S.w1 + (32 * mt + (l & 31)) * kLd1 + 8 * h);
-      floatx16 acc = {};
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb, acc, 0, 0, 0);
-      for (int r = 0; r < 16; ++r) ha[mt][r] = fmaxf(acc[r] + S.b[32 * mt + 8 * (r >> 2) + 4 * h + (r & 3)], 0.f);
-    }
-    if (H1) fused_store(H1, row, rows, ha, l);
-    fused_hidden(S.w2, S.b + kHidden, ha, hb, l);
-    if (H2) fused_store(H2, row, rows, hb, l);
-    fused_hidden(S.w3, S.b + 2 * kHidden, hb, ha, l);
-    if (H3) fused_store(H3, row, rows, ha, l);
-    // output layer: rows 0..2 of a zero-padded 32-row tile
-    bf16x8 bop[4][2];
-    for (int mt = 0; mt < 4; ++mt)
-      for (int p = 0; p < 2; ++p)
-        for (int t = 0; t < 8; ++t) bop[mt][p][t] = to_bf(ha[mt][8 * p + t]);
-    floatx16 acc = {};
-    const int m = l & 31;
-    for (int q = 0; q < 4; ++q)
-      for (int p = 0; p < 2; ++p) {
-        bf16x8 a;
-        if (m < kOut) a = *reinterpret_cast<const bf16x8*>(S.w4 + m * kLdH + 8 * h + 32 * q + 16 * p);
-        else for (int t = 0; t < 8; ++t) a[t] = __builtin_bit_cast(__bf16, (short)0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop[q][p], acc, 0, 0, 0);
+#pragma unroll
+      for (int g = 0; g < kPair; ++g) {
+        floatx16 acc = {};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[g], acc, 0, 0, 0);
+        hidden_epilogue(acc, S.b, mt, l, ha[g][mt], STORE ? H1 : nullptr, row[g], rows);
       }
-    if (h == 0 && row < rows)
-      for (int k = 0; k < kOut; ++k) Y[row * kOut + k] = acc[k] + S.b[3 * kHidden + k];
+    }
+    fused_hidden(S.w2, S.b + kHidden, ha, hb, l, STORE ? H2 : nullptr, row, rows);
+    fused_hidden(S.w3, S.b + 2 * kHidden, hb, ha, l, STORE ? H3 : nullptr, row, rows);
+    // output layer: rows 0..2 of a 32-row tile whose other rows repeat row 2 and are dropped
+    floatx16 acc[kPair] = {};
+    const __bf16* wrow = S.w4 + min(l & 31, kOut - 1) * kLdH + 8 * h;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
+#pragma unroll
+        for (int g = 0; g < kPair; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, ha[g][q][p], acc[g], 0, 0, 0);
+      }
+#pragma unroll
+    for (int g = 0; g < kPair; ++g)
+      if (h == 0 && on[g] && row[g] < rows)
+        for (int k = 0; k < kOut; ++k) Y[row[g] * kOut + k] = acc[g][k] + S.b[3 * kHidden + k];
   }
 }
 
 void prepare_mlp() {
-  (void)hipFuncSetAttribute((const void*)k_mlp_fused, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
+  (void)hipFuncSetAttribute((const void*)k_mlp_fused<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
+  (void)hipFuncSetAttribute((const void*)k_mlp_fused<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
 }
 
 void launch_mlp_fused(const float* W, const float* norm, const float* X, long rows, const int* need, float* Y,
                       float* H1, float* H2, float* H3, hipStream_t s) {
   if (rows <= 0) return;
-  const long ntiles = (rows + 31) / 32;
-  const long blocks = std::min<long>((ntiles + kWaves - 1) / kWaves, 1024);
-  hipLaunchKernelGGL(k_mlp_fused, dim3((unsigned)blocks), dim3(64 * kWaves), kFusedSmem, s, W, norm, X, rows, need, Y,
-                     H1, H2, H3);
+  const long npairs = ((rows + 31) / 32 + kPair - 1) / kPair;
+  // two workgroups per CU (their LDS); more would stage the weights again
+  const long blocks = std::min<long>((npairs + kWaves - 1) / kWaves, 512);
+  const dim3 g((unsigned)blocks), blk(64 * kWaves);
+  if (H1) hipLaunchKernelGGL(k_mlp_fused<true>, g, blk, kFusedSmem, s, W, norm, X, rows, need, Y, H1, H2, H3);
+  else hipLaunchKernelGGL(k_mlp_fused<false>, g, blk, kFusedSmem, s, W, norm, X, rows, need, Y, H1, H2, H3);
 }
 
 // dH <- dH * (H > 0)
