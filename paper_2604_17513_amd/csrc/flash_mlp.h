@@ -25,18 +25,15 @@ struct MlpLayout {
 };
 static_assert(MlpLayout::total == 35587, "parameter count");
 
-// C = act(op(A) op(B) + bias) with bf16 operands and FP32 accumulation.
-struct GemmArgs {
-  const float* A; long sam, sak;
-  const float* B; long sbk, sbn;
-  float* C; long scm, scn;
-  const float* bias;
-  long M; int N, K;
-  int relu, accumulate;
-  float* work;      // optional split-K scratch (nullptr: no split); work_cap floats
-  long work_cap;
-  int kslice;       // set by launch_gemm
-};
+// Gradient slabs: a workgroup of the gradient kernel takes kGradRows rows at a time and sums into a slab of
+// its own.  At most one workgroup per CU (its LDS), so at most kMaxSlabs slabs.
+constexpr long kGradRows = 128;
+constexpr long kMaxSlabs = 256;
+constexpr long kSlab = (MlpLayout::total + 3) / 4 * 4;
+inline long grad_slabs(long rows) {
+  const long b = (rows + kGradRows - 1) / kGradRows;
+  return b < kMaxSlabs ? b : kMaxSlabs;
+}
 
 // Device buffers of an inference pass over the contact slots of a batch.
 struct MlpBuffers {
@@ -48,18 +45,21 @@ struct MlpBuffers {
   double* lam_ml;      // [rows * 3] cone-projected candidate multipliers
 };
 
-void launch_gemm(const GemmArgs& g, hipStream_t s);
-// Raises the dynamic LDS limit of the fused forward kernel (call once before its first launch).
+// Raises the dynamic LDS limits of the network kernels (call once before their first launch).
 void prepare_mlp();
 // Fused forward pass on the matrix cores: Y = network(X).  norm != nullptr: X holds raw
-// features; need != nullptr: 32-row tiles without a flagged row are skipped; H1..H3 != nullptr:
-// hidden activations stored for the backward pass.
+// features; need != nullptr: 32-row tiles without a flagged row are skipped.
 void launch_mlp_fused(const float* W, const float* norm, const float* X, long rows, const int* need, float* Y,
-                      float* H1, float* H2, float* H3, hipStream_t s);
-void mlp_backward(const float* W, const float* X, long n, const float* H1, const float* H2, const float* H3,
-                  float* dY, float* dA, float* dB, float* G, float* work, long work_cap, hipStream_t s);
-void mlp_loss(const float* Y, const float* Lab, long n, float* dY, double* partial, float* loss, hipStream_t s);
-void launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, int t, hipStream_t s);
+                      hipStream_t s);
+// Mean squared loss of rows (X, Lab) and its gradient; slab: grad_slabs(rows) * kSlab floats, partial:
+// grad_slabs(rows) doubles.
+void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss, float* slab,
+                     double* partial, hipStream_t s);
+// One minibatch of training: rows idx of the raw features and labels, normalised with norm; Adam step t on
+// W, m, v; the loss before the step.
+void launch_mlp_train(float* W, const float* norm, const float* feat, const float* lab, const int* idx, long rows,
+                      float* m, float* v, float lr, int t, float* loss, float* slab, double* partial, hipStream_t s);
+void mlp_loss(const float* Y, const float* Lab, long n, double* partial, float* loss, hipStream_t s);
 void launch_gather_batch(const float* feat, const float* lab, const int* idx, int B, const float* norm, float* X,
                          float* Y, hipStream_t s);
 void launch_col_moments(const float* X, long rows, int cols, double* out, hipStream_t s);

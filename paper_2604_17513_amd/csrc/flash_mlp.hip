@@ -1,6 +1,6 @@
 // Learned warm start: a 16 -> 128 -> 128 -> 128 -> 3 ReLU MLP that predicts the
-// contact multipliers of a step from local features.  Every GEMM runs on the
-// CDNA matrix cores (v_mfma_f32_32x32x8bf16_1k): operands are rounded to
+// contact multipliers of a step from local features.  Every product runs on the
+// CDNA matrix cores (v_mfma_f32_32x32x16_bf16): operands are rounded to
 // bfloat16 (round to nearest even), products accumulate in FP32.  Training
 // keeps FP32 master weights and Adam moments; bias gradients and losses use
 // fixed-order reductions, so a training run is deterministic.
@@ -12,124 +12,7 @@
 
 namespace flash {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ short f2bf(float f) {
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (short)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (short)(u >> 16);
-}
-
-// C(m, n) = act(sum_k A(m, k) B(k, n) + bias[n]) (+ C if accumulate).
-// A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].  One workgroup of 4 waves per
-// 64 x 64 tile of C, each wave a 32 x 32 quadrant on v_mfma_f32_32x32x8bf16_1k (A row = lane % 32,
-// k = 4 (lane / 32) + t; B column = lane % 32, same k; D row = 8 (r / 4) + 4 (lane / 32) + r % 4,
-// column = lane % 32).  K runs in chunks of kKc staged in LDS as bf16, each element rounded once
-// and loaded along whichever of its two indices is contiguous; B is staged transposed so that every
-// MFMA operand is one 8-byte LDS read.  Every quadrant accumulates over k in steps of 8 from the
-// slice start, so the result does not depend on the chunking.
-// blockIdx.z selects a K slice of g.kslice rows when the product is split over K: the slice's
-// partial sums go to g.work[z][M][N] and a second kernel adds the slices in order.
-constexpr int kKc = 32;
-constexpr int kKp = kKc + 4;   // padded LDS row (shorts): rows 72 bytes apart
-
-__global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
-  __shared__ short As[64 * kKp];   // [m][k]
-  __shared__ short Bs[64 * kKp];   // [n][k]
-  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-  const long m0 = (long)blockIdx.x * 64, n0 = (long)blockIdx.y * 64;
-  const int wm = 32 * (w & 1), wn = 32 * (w >> 1);
-  const int kb = g.work ? (int)blockIdx.z * g.kslice : 0;
-  const int ke = g.work ? min(g.K, kb + g.kslice) : g.K;
-  const bool a_mfast = g.sam == 1, b_nfast = g.sbn == 1;
-  floatx16 c = {};
-  for (int k0 = kb; k0 < ke; k0 += kKc) {
-    // stage: 64 x kKc of A and of B (8 elements per thread each)
-#pragma unroll
-    for (int q = 0; q < 64 * kKc / 256; ++q) {
-      const int e = tid + 256 * q;
-      const int am = a_mfast ? (e & 63) : (e / kKc), ak = a_mfast ? (e >> 6) : (e % kKc);
-      const long gm = m0 + am;
-      const int gk = k0 + ak;
-      const float av = (gm < g.M && gk < ke) ? g.A[gm * g.sam + (long)gk * g.sak] : 0.f;
-      As[am * kKp + ak] = f2bf(av);
-      const int bn = b_nfast ? (e & 63) : (e / kKc), bk = b_nfast ? (e >> 6) : (e % kKc);
-      const long gn = n0 + bn;
-      const int gk2 = k0 + bk;
-      const float bv = (gn < g.N && gk2 < ke) ? g.B[(long)gk2 * g.sbk + gn * g.sbn] : 0.f;
-      Bs[bn * kKp + bk] = f2bf(bv);
-    }
-    __syncthreads();
-    const int kend = min(kKc, ke - k0);
-    for (int kk = 0; kk < kend; kk += 8) {
-      const int ko = kk + 4 * (l >> 5);
-      const bf16x4 a = *reinterpret_cast<const bf16x4*>(&As[(wm + (l & 31)) * kKp + ko]);
-      const bf16x4 b = *reinterpret_cast<const bf16x4*>(&Bs[(wn + (l & 31)) * kKp + ko]);
-      c = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  const long jj = n0 + wn + (l & 31);
-  if (g.work) {
-    float* wk = g.work + (size_t)blockIdx.z * g.M * g.N;
-    for (int r = 0; r < 16; ++r) {
-      const long ii = m0 + wm + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-      if (ii < g.M && jj < g.N) wk[ii * g.N + jj] = c[r];
-    }
-    return;
-  }
-  for (int r = 0; r < 16; ++r) {
-    const long ii = m0 + wm + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-    if (ii < g.M && jj < g.N) {
-      float v = c[r];
-      if (g.bias) v += g.bias[jj];
-      if (g.relu) v = fmaxf(v, 0.f);
-      float* dst = g.C + ii * g.scm + jj * g.scn;
-      *dst = g.accumulate ? *dst + v : v;
-    }
-  }
-}
-
-// sum of the K slices in slice order, then the epilogue of the plain kernel
-__global__ void k_splitk_reduce(GemmArgs g, int slices) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= g.M * g.N) return;
-  const long ii = idx / g.N, jj = idx - ii * g.N;
-  float v = 0.f;
-  for (int z = 0; z < slices; ++z) v += g.work[(size_t)z * g.M * g.N + idx];
-  if (g.bias) v += g.bias[jj];
-  if (g.relu) v = fmaxf(v, 0.f);
-  float* dst = g.C + ii * g.scm + jj * g.scn;
-  *dst = g.accumulate ? *dst + v : v;
-}
-
-void launch_gemm(const GemmArgs& g0, hipStream_t s) {
-  if (g0.M <= 0 || g0.N <= 0) return;
-  GemmArgs g = g0;
-  dim3 grid((unsigned)((g.M + 63) / 64), (unsigned)((g.N + 63) / 64));
-  // few output tiles over a long K (weight gradients): split K so that the chip fills.  The slice
-  // count is the one chosen for 32 x 32 tiles, so the slices (hence the bits) are those of that
-  // tiling.
-  const long tiles32 = ((g.M + 31) / 32) * (long)((g.N + 31) / 32);
-  int slices = 1;
-  if (g.work && tiles32 < 512 && g.K > 256) {
-    slices = (int)std::min<long>((g.K + 127) / 128, std::max<long>(1, 1024 / tiles32));
-    slices = std::min<long>(slices, g.work_cap / (g.M * g.N));
-  }
-  if (slices <= 1) {
-    g.work = nullptr;
-    hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, s, g);
-    return;
-  }
-  g.kslice = ((g.K + slices - 1) / slices + 7) / 8 * 8;
-  slices = (g.K + g.kslice - 1) / g.kslice;
-  grid.z = (unsigned)slices;
-  hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, s, g);
-  const long mn = g.M * g.N;
-  hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, g, slices);
-}
 
 // ---------------------------------------------------------------------------
 // Fused forward pass on v_mfma_f32_32x32x16_bf16.  Lane layout of that
@@ -155,13 +38,14 @@ struct FusedSmem {
   __bf16 w3[kHidden * kLdH];
   __bf16 w4[kOut * kLdH];
   alignas(16) float b[3 * kHidden + 4];
-  float nrm[2 * kFeat];
+  float nrm[kNorm + 1];
 };
 constexpr size_t kFusedSmem = sizeof(FusedSmem);
 
 __device__ __forceinline__ int perm16(int c) { return (c & ~12) | ((c & 4) << 1) | ((c & 8) >> 1); }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 // Two floats to bf16 (nearest even) in one instruction.
@@ -175,6 +59,7 @@ __device__ __forceinline__ bf16x2 to_bf2(float a, float b) {
 template <bool PERM, int U>
 __device__ __forceinline__ void stage_weights(const float* W, int rows, int cols, __bf16* dst, int ld) {
   const int n4 = rows * cols / 4;
+#pragma unroll 1
   for (int i0 = threadIdx.x; i0 < n4; i0 += U * blockDim.x) {
     float4 v[U];
 #pragma unroll
@@ -194,28 +79,11 @@ __device__ __forceinline__ void stage_weights(const float* W, int rows, int cols
   }
 }
 
-// Tiles (of 32 rows) a wave takes together: they share every A operand read from LDS.
+// Tiles (of 32 rows) a wave of the forward pass takes together: they share every A operand read from LDS.
 constexpr int kPair = 2;
 
-// Bias, ReLU and rounding of one 32-neuron output tile mt: the next layer's operands (and with H the
-// activations of row `row`, when it is below rows).
-__device__ __forceinline__ void hidden_epilogue(const floatx16& acc, const float* bias, int mt, int l, bf16x8 (&out)[2],
-                                                float* H, long row, long rows) {
-  float v[16];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 b = *reinterpret_cast<const float4*>(bias + 32 * mt + 8 * q + 4 * (l >> 5));
-    v[4 * q] = fmaxf(acc[4 * q] + b.x, 0.f);
-    v[4 * q + 1] = fmaxf(acc[4 * q + 1] + b.y, 0.f);
-    v[4 * q + 2] = fmaxf(acc[4 * q + 2] + b.z, 0.f);
-    v[4 * q + 3] = fmaxf(acc[4 * q + 3] + b.w, 0.f);
-  }
-  if (H && row < rows) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<float4*>(H + row * kHidden + 32 * mt + 8 * q + 4 * (l >> 5)) =
-          make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-  }
+// The 16 values a lane holds of a tile, rounded to the next product's operands.
+__device__ __forceinline__ void round_tile(const float (&v)[16], bf16x8 (&out)[2]) {
 #pragma unroll
   for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -226,56 +94,131 @@ __device__ __forceinline__ void hidden_epilogue(const floatx16& acc, const float
     }
 }
 
-// One hidden layer of a wave's kPair tiles: out = relu(W in + b), in and out as operands.
-__device__ __forceinline__ void fused_hidden(const __bf16* w, const float* bias, const bf16x8 (&in)[kPair][4][2],
-                                             bf16x8 (&out)[kPair][4][2], int l, float* H, const long (&row)[kPair],
-                                             long rows) {
+// Bias, ReLU and rounding of one 32-neuron output tile mt: the next layer's operands, and bit r of
+// the result set where register r's value is positive.
+__device__ __forceinline__ unsigned hidden_epilogue(const floatx16& acc, const float* bias, int mt, int l,
+                                                    bf16x8 (&out)[2]) {
+  float v[16];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 b = *reinterpret_cast<const float4*>(bias + 32 * mt + 8 * q + 4 * (l >> 5));
+    v[4 * q] = fmaxf(acc[4 * q] + b.x, 0.f);
+    v[4 * q + 1] = fmaxf(acc[4 * q + 1] + b.y, 0.f);
+    v[4 * q + 2] = fmaxf(acc[4 * q + 2] + b.z, 0.f);
+    v[4 * q + 3] = fmaxf(acc[4 * q + 3] + b.w, 0.f);
+  }
+  unsigned mask = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) mask |= v[r] > 0.f ? 1u << r : 0u;
+  round_tile(v, out);
+  return mask;
+}
+
+// One hidden layer of a wave's G tiles: out = relu(W in + b), in and out as operands.
+template <int G>
+__device__ __forceinline__ void fused_hidden(const __bf16* w, const float* bias, const bf16x8 (&in)[G][4][2],
+                                             bf16x8 (&out)[G][4][2], int l, unsigned (&mask)[G][4]) {
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
     const __bf16* wrow = w + (32 * mt + (l & 31)) * kLdH + 8 * (l >> 5);
-    floatx16 acc[kPair] = {};
+    floatx16 acc[G] = {};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
 #pragma unroll
-        for (int g = 0; g < kPair; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, in[g][q][p], acc[g], 0, 0, 0);
+        for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, in[g][q][p], acc[g], 0, 0, 0);
       }
 #pragma unroll
-    for (int g = 0; g < kPair; ++g) hidden_epilogue(acc[g], bias, mt, l, out[g][mt], H, row[g], rows);
+    for (int g = 0; g < G; ++g) mask[g][mt] = hidden_epilogue(acc[g], bias, mt, l, out[g][mt]);
   }
+}
+
+// First and last layer's weights, biases and feature scales to LDS.
+template <class S>
+__device__ __forceinline__ void stage_small(S& sm, const float* W, const float* norm) {
+  const MlpLayout L;
+  const int tid = threadIdx.x;
+  stage_weights<false, 2>(W + L.w1, kHidden, kFeat, sm.w1, kLd1);
+  stage_weights<true, 1>(W + L.w4, kOut, kHidden, sm.w4, kLdH);
+  for (int i = tid; i < kHidden; i += blockDim.x) {
+    sm.b[i] = W[L.b1 + i];
+    sm.b[kHidden + i] = W[L.b2 + i];
+    sm.b[2 * kHidden + i] = W[L.b3 + i];
+  }
+  if (tid < kOut) sm.b[3 * kHidden + tid] = W[L.b4 + tid];
+  if (tid < kNorm) sm.nrm[tid] = norm ? norm[tid] : (tid < kFeat ? 0.f : 1.f);
+}
+
+// The 8 features a lane holds of one sample, normalised and rounded.
+template <class S>
+__device__ __forceinline__ bf16x8 feature_operand(const S& sm, const float* x, int h) {
+  float v[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = x[8 * h + t];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = (v[t] - sm.nrm[8 * h + t]) * sm.nrm[kFeat + 8 * h + t];
+  bf16x8 out;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const bf16x2 c = to_bf2(v[2 * t], v[2 * t + 1]);
+    out[2 * t] = c[0];
+    out[2 * t + 1] = c[1];
+  }
+  return out;
+}
+
+// The four layers on a wave's G tiles: the operands of the hidden layers in h1..h3 (two of them may be the
+// same array), positive-value masks, and the output tile (rows 0..2; the others repeat row 2).
+template <int G, class S>
+__device__ __forceinline__ void network(const S& sm, const bf16x8 (&xb)[G], int l, bf16x8 (&h1)[G][4][2],
+                                        bf16x8 (&h2)[G][4][2], bf16x8 (&h3)[G][4][2], unsigned (&m1)[G][4],
+                                        unsigned (&m2)[G][4], unsigned (&m3)[G][4], floatx16 (&y)[G]) {
+  const int h = l >> 5;
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const bf16x8 a = *reinterpret_cast<const bf16x8*>(sm.w1 + (32 * mt + (l & 31)) * kLd1 + 8 * h);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      floatx16 acc = {};
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[g], acc, 0, 0, 0);
+      m1[g][mt] = hidden_epilogue(acc, sm.b, mt, l, h1[g][mt]);
+    }
+  }
+  fused_hidden<G>(sm.w2, sm.b + kHidden, h1, h2, l, m2);
+  fused_hidden<G>(sm.w3, sm.b + 2 * kHidden, h2, h3, l, m3);
+  const __bf16* wrow = sm.w4 + min(l & 31, kOut - 1) * kLdH + 8 * h;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (q + p == 0) y[g] = floatx16{};
+        y[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, h3[g][q][p], y[g], 0, 0, 0);
+      }
+    }
 }
 
 // Y = network(X) for `rows` rows.  norm != nullptr: X holds raw features, normalised on load.
 // need != nullptr: 32-row tiles without a flagged row are skipped (their Y is left as is).
-// STORE: the hidden activations go to H1, H2, H3 for the backward pass.
 // What bounds it: the matrix cores (76 MFMA of 32 cycles per tile) against about 500 vector instructions of
 // bias, ReLU and rounding; two tiles per wave share the weights' LDS reads and hide each other's chains,
 // and rounding takes half an instruction per value (v_cvt_pk_bf16_f32) instead of six.  One million rows:
 // 81 us a call (0.91 PFLOP/s of network arithmetic), 277 us with one tile per wave and rounding in integer code.
-template <bool STORE>
 __global__ void __launch_bounds__(64 * kWaves, 2) k_mlp_fused(const float* W, const float* norm, const float* X,
-                                                              long rows, const int* need, float* Y, float* H1,
-                                                              float* H2, float* H3) {
+                                                              long rows, const int* need, float* Y) {
   extern __shared__ __align__(16) unsigned char fsm_raw[];
   FusedSmem& S = *reinterpret_cast<FusedSmem*>(fsm_raw);
   const MlpLayout L;
-  const int tid = threadIdx.x;
   stage_weights<true, 8>(W + L.w2, kHidden, kHidden, S.w2, kLdH);
   stage_weights<true, 8>(W + L.w3, kHidden, kHidden, S.w3, kLdH);
-  stage_weights<false, 2>(W + L.w1, kHidden, kFeat, S.w1, kLd1);
-  stage_weights<true, 1>(W + L.w4, kOut, kHidden, S.w4, kLdH);
-  for (int i = tid; i < kHidden; i += blockDim.x) {
-    S.b[i] = W[L.b1 + i];
-    S.b[kHidden + i] = W[L.b2 + i];
-    S.b[2 * kHidden + i] = W[L.b3 + i];
-  }
-  if (tid < kOut) S.b[3 * kHidden + tid] = W[L.b4 + tid];
-  if (tid < 2 * kFeat) S.nrm[tid] = norm ? norm[tid] : (tid < kFeat ? 0.f : 1.f);
+  stage_small(S, W, norm);
   __syncthreads();
 
-  const int l = tid & 63, wave = tid >> 6;
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int h = l >> 5;
   const long npairs = ((rows + 31) / 32 + kPair - 1) / kPair;
   for (long pair = (long)blockIdx.x * kWaves + wave; pair < npairs; pair += (long)gridDim.x * kWaves) {
@@ -290,47 +233,14 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_mlp_fused(const float* W, co
       any |= on[g];
     }
     if (!any) continue;
-    // layer 1: B operand = 8 features of this lane's sample (rows past the end repeat the last one, unused)
     bf16x8 xb[kPair];
 #pragma unroll
-    for (int g = 0; g < kPair; ++g) {
-      const float* x = X + (row[g] < rows ? row[g] : rows - 1) * kFeat + 8 * h;
-      float v[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = x[t];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = (v[t] - S.nrm[8 * h + t]) * S.nrm[kFeat + 8 * h + t];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bf16x2 c = to_bf2(v[2 * t], v[2 * t + 1]);
-        xb[g][2 * t] = c[0];
-        xb[g][2 * t + 1] = c[1];
-      }
-    }
+    for (int g = 0; g < kPair; ++g)   // rows past the end repeat the last one, unused
+      xb[g] = feature_operand(S, X + (row[g] < rows ? row[g] : rows - 1) * kFeat, h);
     bf16x8 ha[kPair][4][2], hb[kPair][4][2];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(S.w1 + (32 * mt + (l & 31)) * kLd1 + 8 * h);
-#pragma unroll
-      for (int g = 0; g < kPair; ++g) {
-        floatx16 acc = {};
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[g], acc, 0, 0, 0);
-        hidden_epilogue(acc, S.b, mt, l, ha[g][mt], STORE ? H1 : nullptr, row[g], rows);
-      }
-    }
-    fused_hidden(S.w2, S.b + kHidden, ha, hb, l, STORE ? H2 : nullptr, row, rows);
-    fused_hidden(S.w3, S.b + 2 * kHidden, hb, ha, l, STORE ? H3 : nullptr, row, rows);
-    // output layer: rows 0..2 of a 32-row tile whose other rows repeat row 2 and are dropped
-    floatx16 acc[kPair] = {};
-    const __bf16* wrow = S.w4 + min(l & 31, kOut - 1) * kLdH + 8 * h;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p);
-#pragma unroll
-        for (int g = 0; g < kPair; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, ha[g][q][p], acc[g], 0, 0, 0);
-      }
+    unsigned mask[kPair][4];
+    floatx16 acc[kPair];
+    network<kPair>(S, xb, l, ha, hb, ha, mask, mask, mask, acc);
 #pragma unroll
     for (int g = 0; g < kPair; ++g)
       if (h == 0 && on[g] && row[g] < rows)
@@ -338,36 +248,389 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_mlp_fused(const float* W, co
   }
 }
 
-void prepare_mlp() {
-  (void)hipFuncSetAttribute((const void*)k_mlp_fused<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
-  (void)hipFuncSetAttribute((const void*)k_mlp_fused<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
-}
-
 void launch_mlp_fused(const float* W, const float* norm, const float* X, long rows, const int* need, float* Y,
-                      float* H1, float* H2, float* H3, hipStream_t s) {
+                      hipStream_t s) {
   if (rows <= 0) return;
   const long npairs = ((rows + 31) / 32 + kPair - 1) / kPair;
   // two workgroups per CU (their LDS); more would stage the weights again
   const long blocks = std::min<long>((npairs + kWaves - 1) / kWaves, 512);
-  const dim3 g((unsigned)blocks), blk(64 * kWaves);
-  if (H1) hipLaunchKernelGGL(k_mlp_fused<true>, g, blk, kFusedSmem, s, W, norm, X, rows, need, Y, H1, H2, H3);
-  else hipLaunchKernelGGL(k_mlp_fused<false>, g, blk, kFusedSmem, s, W, norm, X, rows, need, Y, H1, H2, H3);
+  hipLaunchKernelGGL(k_mlp_fused, dim3((unsigned)blocks), dim3(64 * kWaves), kFusedSmem, s, W, norm, X, rows, need, Y);
 }
 
-// dH <- dH * (H > 0)
-__global__ void k_relu_grad(float* dH, const float* H, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !(H[i] > 0.f)) dH[i] = 0.f;
+// ---------------------------------------------------------------------------
+// Loss and gradient of a minibatch in two launches: k_mlp_grad takes 128 rows per workgroup (32 per wave)
+// through the forward pass, the loss and the whole backward pass, and leaves the block's share of every
+// parameter gradient in the workgroup's slab; k_mlp_reduce adds the slabs in order and, in training, applies
+// Adam.  A wave's activations stay in its registers as bf16 operands; the weight gradients, which contract
+// over rows, take their operands from LDS copies [neuron][row] of one layer at a time.
+// ---------------------------------------------------------------------------
+struct GradSmem {
+  __bf16 w1[kHidden * kLd1];
+  __bf16 w2[kHidden * kLdH];    // W2, then its transpose
+  __bf16 w3[kHidden * kLdH];    // W3, then its transpose
+  __bf16 w4[kOut * kLdH];
+  alignas(16) float b[3 * kHidden + 4];
+  float nrm[kNorm + 1];
+  __bf16 dz[kHidden * kLdH];    // loss gradient of a layer's pre-activations [neuron][row]
+  __bf16 hin[kHidden * kLdH];   // that layer's inputs [neuron][row]
+  float bias[4 * kHidden];      // per-wave sums of dz over rows
+  double e2[kWaves];
+};
+constexpr size_t kGradSmem = sizeof(GradSmem);
+static_assert(kGradSmem <= 160 * 1024, "one workgroup's LDS");
+static_assert(kWaves * 32 == kGradRows, "a wave takes 32 of a block's rows");
+
+// A thread's 2 x 4 blocks of a 128 x 128 weight matrix.  A wave spans 8 block rows and 8 block columns, so that
+// the loads are whole 128-byte lines and both LDS forms, rows and transposed rows, are free of bank conflicts.
+constexpr int kBlocks = kHidden * kHidden / 8 / (64 * kWaves);
+__device__ __forceinline__ int block_row(int u) {
+  const int i = threadIdx.x + u * 64 * kWaves;
+  return 2 * (((i >> 3) & 7) + 8 * (i >> 8));
+}
+__device__ __forceinline__ int block_col(int u) {
+  const int i = threadIdx.x + u * 64 * kWaves;
+  return 4 * ((i & 7) + 8 * ((i >> 6) & 3));
+}
+static_assert(kWaves == 4 && kBlocks == 8, "the block maps");
+
+__device__ __forceinline__ void load_blocks(const float* W, float (&f)[kBlocks][8]) {
+#pragma unroll
+  for (int u = 0; u < kBlocks; ++u) {
+    const float* src = W + block_row(u) * kHidden + block_col(u);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      f[u][t] = src[t];
+      f[u][4 + t] = src[kHidden + t];
+    }
+  }
 }
 
-// dY = 2 (Y - L) / (rows * 3); per-block partial sums of (Y - L)^2 in fixed order
-__global__ void k_mse(const float* Y, const float* L, long n, float* dY, double* partial) {
+// Rounded rows of W to LDS (columns permuted by perm16).
+__device__ __forceinline__ void put_blocks(const float (&f)[kBlocks][8], __bf16* dst) {
+#pragma unroll
+  for (int u = 0; u < kBlocks; ++u)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      bf16x2* d = reinterpret_cast<bf16x2*>(dst + (block_row(u) + i) * kLdH + perm16(block_col(u)));
+      d[0] = to_bf2(f[u][4 * i], f[u][4 * i + 1]);
+      d[1] = to_bf2(f[u][4 * i + 2], f[u][4 * i + 3]);
+    }
+}
+
+// From those rows to registers, and back as rows of the transpose (the outputs, its columns, permuted).
+__device__ __forceinline__ void read_blocks(const __bf16* src, bf16x4 (&w)[kBlocks][2]) {
+#pragma unroll
+  for (int u = 0; u < kBlocks; ++u)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      w[u][i] = *reinterpret_cast<const bf16x4*>(src + (block_row(u) + i) * kLdH + perm16(block_col(u)));
+}
+__device__ __forceinline__ void put_transposed(const bf16x4 (&w)[kBlocks][2], __bf16* dst) {
+#pragma unroll
+  for (int u = 0; u < kBlocks; ++u)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const bf16x2 c = {w[u][0][t], w[u][1][t]};
+      *reinterpret_cast<bf16x2*>(dst + (block_col(u) + t) * kLdH + perm16(block_row(u))) = c;
+    }
+}
+
+// A wave's operands of one layer to [neuron][row] form, rows past the end as zeros.
+__device__ __forceinline__ void put_rows(__bf16* dst, const bf16x8 (&op)[4][2], int col, int h, bool valid) {
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        dst[(32 * mt + 16 * p + 8 * (t >> 2) + 4 * h + (t & 3)) * kLdH + col] = valid ? op[mt][p][t] : (__bf16)0.f;
+}
+
+// One exchange of bias_sums: of 2 N values each lane keeps N, added to its partner's.
+template <int N, int S>
+__device__ __forceinline__ void halve(float (&v)[16], int l) {
+  const bool up = (l & S) != 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float keep = up ? v[i + N] : v[i], give = up ? v[i] : v[i + N];
+    v[i] = keep + __shfl_xor(give, S);
+  }
+}
+
+// Sums of a tile's 16 neurons over the wave's rows, halving the values a lane holds at each exchange.
+__device__ __forceinline__ void bias_sums(float (&v)[16], float* dst, int mt, int l) {
+  halve<8, 16>(v, l);
+  halve<4, 8>(v, l);
+  halve<2, 4>(v, l);
+  halve<1, 2>(v, l);
+  v[0] += __shfl_xor(v[0], 1);
+  const int r = (l & 31) >> 1;
+  if ((l & 1) == 0) dst[32 * mt + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)] = v[0];
+}
+
+// ReLU mask, bias sums and rounding of one tile of dz.
+__device__ __forceinline__ void dz_tile(const floatx16& acc, unsigned mask, int mt, int l, float* bias, bf16x8 (&out)[2]) {
+  float v[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = (mask >> r) & 1u ? acc[r] : 0.f;
+  round_tile(v, out);
+  bias_sums(v, bias, mt, l);
+}
+
+// dz of the layer below from this layer's (operands din) through the transposed weights wt.
+__device__ __forceinline__ void dz_below(const __bf16* wt, const bf16x8 (&din)[4][2], const unsigned (&mask)[4], int l,
+                                         float* bias, bf16x8 (&dout)[4][2]) {
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const __bf16* wrow = wt + (32 * mt + (l & 31)) * kLdH + 8 * (l >> 5);
+    floatx16 acc = {};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p),
+                                                      din[q][p], acc, 0, 0, 0);
+    dz_tile(acc, mask[mt], mt, l, bias, dout[mt]);
+    __builtin_amdgcn_sched_barrier(0);   // one tile's operands in flight, not all four's
+  }
+}
+
+// One 32 x 32 tile of dz hin^T over the block's rows; mrow, nrow: this lane's rows of the two operands.
+__device__ __forceinline__ floatx16 row_product(const __bf16* mrow, const __bf16* nrow) {
+  floatx16 acc = {};
+#pragma unroll
+  for (int k = 0; k < kGradRows; k += 16)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(mrow + k),
+                                                  *reinterpret_cast<const bf16x8*>(nrow + k), acc, 0, 0, 0);
+  return acc;
+}
+
+__device__ __forceinline__ void put(float* p, float v, bool first) { *p = first ? v : *p + v; }
+
+// A lane's 16 values of a 32 x 32 tile to column c of G (row stride ld).
+__device__ __forceinline__ void put_tile(float* G, int ld, int row0, int c, int h, const floatx16& v, bool first) {
+  float* p = G + (row0 + 4 * h) * ld + c;
+  if (first) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * ld] = v[r];
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * ld] += v[r];
+  }
+}
+
+// The 128 x 128 weight gradient of a hidden layer: wave w takes the 32 inputs 32 w .. and all outputs.
+__device__ __forceinline__ void hidden_wgrad(const GradSmem& S, float* G, int l, int wave, bool first) {
+  const int h = l >> 5, c = 32 * wave + (l & 31);
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const floatx16 acc = row_product(S.dz + (32 * mt + (l & 31)) * kLdH + 8 * h, S.hin + c * kLdH + 8 * h);
+    put_tile(G, kHidden, 32 * mt, c, h, acc, first);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+__device__ __forceinline__ void put_bias(const GradSmem& S, float* G, bool first) {
+  const int t = threadIdx.x;
+  if (t < kHidden)
+    put(G + t, (S.bias[t] + S.bias[kHidden + t]) + (S.bias[2 * kHidden + t] + S.bias[3 * kHidden + t]), first);
+}
+
+// Rows idx[r] (or r) of feat and lab, normalised with norm (or as they are).  Workgroup b takes the blocks of
+// kGradRows rows b, b + gridDim.x, ...; its sums go to slab[b][MlpLayout] and partial[b] (squared errors).
+// What bounds it: latency of one wave per SIMD through ten dependent products, then LDS traffic of the
+// [neuron][row] copies; activations and their gradients never reach memory.  A minibatch of 4096 (32
+// workgroups): 25 us and 5 us for the reduction; separate kernels per product, mask, sum and layer (21 launches,
+// activations through memory) took 300 us.  Of the 25: weights 2, forward pass 4, transposing 1.5, the three
+// dz layers 2.2 each, the weight gradients 1.5 each, row copies 0.6 each.
+__global__ void __launch_bounds__(64 * kWaves, 1) k_mlp_grad(const float* W, const float* norm, const float* feat,
+                                                             const float* lab, const int* idx, long rows, float* slab,
+                                                             double* partial) {
+  extern __shared__ __align__(16) unsigned char gsm_raw[];
+  GradSmem& S = *reinterpret_cast<GradSmem*>(gsm_raw);
+  const MlpLayout L;
+  const int wave = threadIdx.x >> 6;
+  const long nblk = (rows + kGradRows - 1) / kGradRows;
+  float* G = slab + (size_t)blockIdx.x * kSlab;
+  float* wbias = S.bias + wave * kHidden;
+  for (long blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    const bool first = blk == blockIdx.x;
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));   // addresses are formed where they are used, not kept through the loop
+    const int h = l >> 5;
+    const int col = 32 * wave + (l & 31);   // this lane's row within the block
+    {
+      float f2[kBlocks][8], f3[kBlocks][8];
+      load_blocks(W + L.w2, f2);
+      load_blocks(W + L.w3, f3);
+      stage_small(S, W, norm);
+      put_blocks(f2, S.w2);
+      put_blocks(f3, S.w3);
+    }
+    const long row = blk * kGradRows + col;
+    const bool valid = row < rows;
+    const long at = valid ? row : rows - 1;
+    const long src = idx ? idx[at] : at;
+    float target[kOut];
+    for (int k = 0; k < kOut; ++k) target[k] = lab[src * kOut + k];
+    __syncthreads();
+    bf16x8 xb[1] = {feature_operand(S, feat + src * kFeat, h)};
+    bf16x8 h1[1][4][2], h2[1][4][2], h3[1][4][2];
+    unsigned m1[1][4], m2[1][4], m3[1][4];
+    floatx16 y[1];
+    network<1>(S, xb, l, h1, h2, h3, m1, m2, m3, y);
+    if (!valid)
+      for (int mt = 0; mt < 4; ++mt) m1[0][mt] = m2[0][mt] = m3[0][mt] = 0;
+    // loss: the lower half of the lanes holds the outputs
+    float dy[kOut];
+    double e2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) {
+      const float d = (y[0][k] + S.b[3 * kHidden + k]) - target[k] * S.nrm[2 * kFeat + k];
+      const bool on = valid & (h == 0);
+      dy[k] = on ? 2.f * d / (float)(rows * kOut) : 0.f;
+      e2 += on ? (double)d * d : 0.0;
+    }
+    for (int s = 32; s > 0; s >>= 1) e2 += __shfl_xor(e2, s);
+    if (l == 0) S.e2[wave] = e2;
+    // output layer: its inputs and dy to LDS; dz3 (= W4^T dy) needs no transposed copy
+    bf16x8 dyb;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) dyb[t] = (__bf16)0.f;
+    const bf16x2 d01 = to_bf2(dy[0], dy[1]), d2 = to_bf2(dy[2], 0.f);
+    dyb[0] = d01[0];
+    dyb[1] = d01[1];
+    dyb[2] = d2[0];
+    if (h == 0)
+#pragma unroll
+      for (int k = 0; k < kOut; ++k) S.dz[k * kLdH + col] = dyb[k];
+    put_rows(S.hin, h3[0], col, h, valid);
+    float db4[kOut];
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) {
+      db4[k] = dy[k];
+      for (int s = 16; s > 0; s >>= 1) db4[k] += __shfl_xor(db4[k], s);
+      if (l == 0) wbias[k] = db4[k];
+    }
+    __syncthreads();   // forward weights free, dy and h3 written
+    {
+      const floatx16 acc = row_product(S.dz + min(l & 31, kOut - 1) * kLdH + 8 * h, S.hin + col * kLdH + 8 * h);
+      if (h == 0)
+#pragma unroll
+        for (int k = 0; k < kOut; ++k) put(G + L.w4 + k * kHidden + col, acc[k], first);
+      const int t = threadIdx.x;
+      if (t < kOut)
+        put(G + L.b4 + t, (S.bias[t] + S.bias[kHidden + t]) + (S.bias[2 * kHidden + t] + S.bias[3 * kHidden + t]), first);
+      if (t == 0) partial[blockIdx.x] = (first ? 0.0 : partial[blockIdx.x]) + ((S.e2[0] + S.e2[1]) + (S.e2[2] + S.e2[3]));
+    }
+    bf16x4 w2[kBlocks][2], w3[kBlocks][2];
+    read_blocks(S.w3, w3);
+    read_blocks(S.w2, w2);
+    bf16x8 w4t[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        w4t[mt][t] = t < kOut ? (h == 0 ? S.w4[t * kLdH + perm16(32 * mt + (l & 31))] : (__bf16)0.f) : (__bf16)0.f;
+    __syncthreads();   // dy, h3, the weights' rows and the bias sums read
+    put_transposed(w3, S.w3);
+    put_transposed(w2, S.w2);
+    bf16x8 dz3[4][2], dz2[4][2], dz1[4][2];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      floatx16 acc = {};
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w4t[mt], dyb, acc, 0, 0, 0);
+      dz_tile(acc, m3[0][mt], mt, l, wbias, dz3[mt]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    put_rows(S.dz, dz3, col, h, true);
+    put_rows(S.hin, h2[0], col, h, valid);
+    __syncthreads();
+    put_bias(S, G + L.b3, first);
+    hidden_wgrad(S, G + L.w3, l, wave, first);
+    __syncthreads();
+    dz_below(S.w3, dz3, m2[0], l, wbias, dz2);
+    put_rows(S.dz, dz2, col, h, true);
+    put_rows(S.hin, h1[0], col, h, valid);
+    __syncthreads();
+    put_bias(S, G + L.b2, first);
+    hidden_wgrad(S, G + L.w2, l, wave, first);
+    __syncthreads();
+    dz_below(S.w2, dz2, m1[0], l, wbias, dz1);
+    put_rows(S.dz, dz1, col, h, true);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) S.hin[(8 * h + t) * kLdH + col] = valid ? xb[0][t] : (__bf16)0.f;
+    __syncthreads();
+    put_bias(S, G + L.b1, first);
+    const floatx16 acc = row_product(S.dz + col * kLdH + 8 * h, S.hin + min(l & 31, kFeat - 1) * kLdH + 8 * h);
+    if ((l & 31) < kFeat) put_tile(G + L.w1, kFeat, 32 * wave, l & 31, h, acc, first);
+    __syncthreads();
+  }
+}
+
+// Gradient = sum of the slabs in order: to grad, or (p != nullptr) straight into an Adam step on p, m, v.
+// The first wave adds the squared errors: loss = sum / n.
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float* slab, int slabs, const double* partial, long n,
+                                                    float* loss, float* grad, float* p, float* m, float* v, float lr,
+                                                    float b1, float b2, float eps, float c1, float c2) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    double s = 0.0;
+    for (int b = threadIdx.x; b < slabs; b += 64) s += partial[b];
+    for (int k = 32; k > 0; k >>= 1) s += __shfl_xor(s, k);
+    if (threadIdx.x == 0) *loss = (float)(s / (double)n);
+  }
+  if (i >= (int)MlpLayout::total) return;
+  float gi = 0.f;
+#pragma unroll 16
+  for (int b = 0; b < slabs; ++b) gi += slab[(size_t)b * kSlab + i];
+  if (!p) {
+    grad[i] = gi;
+    return;
+  }
+  const float mi = b1 * m[i] + (1.f - b1) * gi;
+  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+  m[i] = mi;
+  v[i] = vi;
+  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+}
+
+void prepare_mlp() {
+  (void)hipFuncSetAttribute((const void*)k_mlp_fused, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedSmem);
+  (void)hipFuncSetAttribute((const void*)k_mlp_grad, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGradSmem);
+}
+
+static void launch_grad_blocks(const float* W, const float* norm, const float* feat, const float* lab, const int* idx,
+                               long rows, float* slab, double* partial, hipStream_t s) {
+  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)grad_slabs(rows)), dim3(64 * kWaves), kGradSmem, s, W, norm, feat, lab,
+                     idx, rows, slab, partial);
+}
+
+constexpr unsigned kReduceGrid = (unsigned)((MlpLayout::total + 255) / 256);
+
+void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss, float* slab,
+                     double* partial, hipStream_t s) {
+  launch_grad_blocks(W, nullptr, X, Lab, nullptr, rows, slab, partial, s);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(256), 0, s, slab, (int)grad_slabs(rows), partial,
+                     kOut * rows, loss, grad, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
+}
+
+void launch_mlp_train(float* W, const float* norm, const float* feat, const float* lab, const int* idx, long rows,
+                      float* m, float* v, float lr, int t, float* loss, float* slab, double* partial, hipStream_t s) {
+  const float b1 = 0.9f, b2 = 0.999f;
+  const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
+  launch_grad_blocks(W, norm, feat, lab, idx, rows, slab, partial, s);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(256), 0, s, slab, (int)grad_slabs(rows), partial,
+                     kOut * rows, loss, nullptr, W, m, v, lr, b1, b2, 1e-8f, c1, c2);
+}
+
+// per-block partial sums of (Y - L)^2 in fixed order
+__global__ void k_mse(const float* Y, const float* L, long n, double* partial) {
   __shared__ double sh[256];
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   double e2 = 0.0;
   if (i < n) {
     const float d = Y[i] - L[i];
-    dY[i] = 2.f * d / (float)n;
     e2 = (double)d * d;
   }
   sh[threadIdx.x] = e2;
@@ -387,34 +650,7 @@ __global__ void k_sum_partials(const double* partial, int nb, long n, float* los
   }
 }
 
-// out[c] = sum_r X[r * ld + c], one block per column, fixed tree order
-__global__ void k_colsum(const float* X, long rows, int ld, float* out) {
-  __shared__ float sh[256];
-  const int c = blockIdx.x;
-  float s = 0.f;
-  for (long r = threadIdx.x; r < rows; r += 256) s += X[r * ld + c];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[c] = sh[0];
-}
-
-__global__ void k_adam(float* p, const float* g, float* m, float* v, int n, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-// minibatch gather with feature / label normalisation
+// rows idx of the data with feature / label normalisation
 __global__ void k_gather_batch(const float* feat, const float* lab, const int* idx, int B, const float* norm,
                                float* X, float* Y) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -424,58 +660,11 @@ __global__ void k_gather_batch(const float* feat, const float* lab, const int* i
   for (int k = 0; k < 3; ++k) Y[r * 3 + k] = lab[s * 3 + k] * norm[2 * kFeat + k];
 }
 
-// ---------------------------------------------------------------------------
-// forward / backward of the network on row-major activations
-// ---------------------------------------------------------------------------
-// grads of the mean-squared loss; dY holds dLoss/dY on entry (overwritten scratch: dA, dB)
-void mlp_backward(const float* W, const float* X, long n, const float* H1, const float* H2, const float* H3,
-                  float* dY, float* dA, float* dB, float* G, float* work, long work_cap, hipStream_t s) {
-  const MlpLayout L;
-  // dW = dZ^T * Hin  (nout x nin), db = colsum(dZ)
-  auto wgrad = [&](const float* dZ, int nout, const float* Hin, int nin, float* dW, float* db) {
-    GemmArgs g{};
-    g.M = nout; g.N = nin; g.K = (int)n;
-    g.A = dZ; g.sam = 1; g.sak = nout;   // A(m, k) = dZ[k][m]
-    g.B = Hin; g.sbk = nin; g.sbn = 1;   // B(k, n) = Hin[k][n]
-    g.C = dW; g.scm = nin; g.scn = 1;
-    g.work = work; g.work_cap = work_cap;
-    launch_gemm(g, s);
-    hipLaunchKernelGGL(k_colsum, dim3(nout), dim3(256), 0, s, dZ, n, nout, db);
-  };
-  // dHin = dZ * W (n x nin)
-  auto dgrad = [&](const float* dZ, int nout, const float* w, int nin, float* dH) {
-    GemmArgs g{};
-    g.M = n; g.N = nin; g.K = nout;
-    g.A = dZ; g.sam = nout; g.sak = 1;
-    g.B = w; g.sbk = nin; g.sbn = 1;     // B(k, n) = W[k][n]
-    g.C = dH; g.scm = nin; g.scn = 1;
-    launch_gemm(g, s);
-  };
-  const long nh = n * kHidden;
-  const unsigned gb = (unsigned)((nh + 255) / 256);
-  wgrad(dY, 3, H3, kHidden, G + L.w4, G + L.b4);
-  dgrad(dY, 3, W + L.w4, kHidden, dA);
-  hipLaunchKernelGGL(k_relu_grad, dim3(gb), dim3(256), 0, s, dA, H3, nh);
-  wgrad(dA, kHidden, H2, kHidden, G + L.w3, G + L.b3);
-  dgrad(dA, kHidden, W + L.w3, kHidden, dB);
-  hipLaunchKernelGGL(k_relu_grad, dim3(gb), dim3(256), 0, s, dB, H2, nh);
-  wgrad(dB, kHidden, H1, kHidden, G + L.w2, G + L.b2);
-  dgrad(dB, kHidden, W + L.w2, kHidden, dA);
-  hipLaunchKernelGGL(k_relu_grad, dim3(gb), dim3(256), 0, s, dA, H1, nh);
-  wgrad(dA, kHidden, X, kFeat, G + L.w1, G + L.b1);
-}
-
-void mlp_loss(const float* Y, const float* Lab, long n, float* dY, double* partial, float* loss, hipStream_t s) {
+void mlp_loss(const float* Y, const float* Lab, long n, double* partial, float* loss, hipStream_t s) {
   const long m = 3 * n;
   const int nb = (int)((m + 255) / 256);
-  hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, Y, Lab, m, dY, partial);
+  hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, Y, Lab, m, partial);
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1), 0, s, partial, nb, m, loss);
-}
-
-void launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, int t, hipStream_t s) {
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-  hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, p, g, m, v, n, lr, b1, b2, 1e-8f, c1, c2);
 }
 
 void launch_gather_batch(const float* feat, const float* lab, const int* idx, int B, const float* norm, float* X,
@@ -645,7 +834,7 @@ void launch_ws_labels(const DevBatch<T>& B, const float* feat, float* lab, hipSt
 template <class T>
 void launch_ws_infer(const DevBatch<T>& B, const T* mu_env, const MlpBuffers& M, hipStream_t s) {
   const long n = (long)B.n_envs * B.cap;
-  launch_mlp_fused(M.W, M.norm, M.feat, n, M.need, M.Y, nullptr, nullptr, nullptr, s);
+  launch_mlp_fused(M.W, M.norm, M.feat, n, M.need, M.Y, s);
   hipLaunchKernelGGL(k_ws_candidates<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, B, mu_env, M.feat, M.Y,
                      M.norm, M.lam_ml);
 }

@@ -1,8 +1,9 @@
 // C ABI of the warm-start network trainer: device-resident FP32 master weights,
-// Adam moments and minibatch scratch; every forward and backward GEMM runs in
-// the bf16 MFMA kernel of flash_mlp.hip.
+// Adam moments and gradient slabs; every forward and backward product runs in
+// the bf16 MFMA kernels of flash_mlp.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -48,23 +49,17 @@ uint16_t to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Scratch of flash_mlp_grad_noalloc, one copy per GPU for the life of the process: the
-// hidden activations H1..H3 and the backward buffers dA, dB (rows x 128 floats each), the
-// network output and its loss gradient (rows x 3 each), the split-K partial sums of the weight
-// gradients (the trainer's size, so that both entry points split every product the same way)
-// and the per-block loss partials.
+// Scratch of flash_mlp_grad_noalloc, one copy per GPU for the life of the process: the gradient
+// slabs (the trainer's, so that both entry points sum every gradient in the same order), the
+// squared-error sums and a loss slot for callers that want none.
 constexpr long kNaRows = 2048;
-constexpr long kNaWork = 64L * kHidden * kHidden;
-constexpr long kNaPartials = (3 * kNaRows + 255) / 256 + 1;
-constexpr size_t kNaHid = (size_t)kNaRows * kHidden * sizeof(float);
-constexpr size_t kNaOut = (size_t)kNaRows * kOut * sizeof(float);
+constexpr long kNaSlabs = kNaRows / kGradRows;
+static_assert(kNaRows % kGradRows == 0 && kNaSlabs <= kMaxSlabs, "one slab per block of rows");
 constexpr size_t kNaOffPartial = 0;
-constexpr size_t kNaOffH = 256;
-constexpr size_t kNaOffY = kNaOffH + 5 * kNaHid;
-constexpr size_t kNaOffWork = kNaOffY + 2 * kNaOut + 256;
-constexpr size_t kNaBytes = kNaOffWork + (size_t)kNaWork * sizeof(float);
-static_assert(kNaPartials * sizeof(double) <= kNaOffH, "loss partials fit their slot");
-static_assert(kNaOffWork % 256 == 0 && kNaOffY % 256 == 0, "aligned scratch regions");
+constexpr size_t kNaOffLoss = 256;
+constexpr size_t kNaOffSlab = 512;
+constexpr size_t kNaBytes = kNaOffSlab + (size_t)kNaSlabs * kSlab * sizeof(float);
+static_assert(kNaSlabs * sizeof(double) <= kNaOffLoss, "squared-error sums fit their slot");
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
@@ -94,12 +89,10 @@ struct flash_mlp {
   bool own_stream = false;
   std::vector<void*> own;
   float *W = nullptr, *G = nullptr, *Mo = nullptr, *Vo = nullptr, *norm = nullptr;
-  float *X = nullptr, *L = nullptr, *H1 = nullptr, *H2 = nullptr, *H3 = nullptr, *Y = nullptr, *dY = nullptr;
-  float *dA = nullptr, *dB = nullptr, *loss = nullptr;
+  float *X = nullptr, *L = nullptr, *Y = nullptr, *loss = nullptr;   // evaluation chunks, minibatch losses
+  float* slab = nullptr;                       // per-workgroup sums of the parameter gradients
   double* partial = nullptr;
   double* moments = nullptr;
-  float* work = nullptr;                       // split-K partial sums of the weight gradients
-  static constexpr long kWork = 64L * kHidden * kHidden;
   int adam_t = 0;
   std::vector<float> host_norm;
 
@@ -113,16 +106,7 @@ struct flash_mlp {
     HIPCHK(hipMemsetAsync(Vo, 0, MlpLayout::total * sizeof(float), stream));
     adam_t = 0;
   }
-
-  // loss and gradient of one minibatch already in X (normalised) and L (scaled labels)
-  void grad(long n, float* loss_dst) {
-    launch_mlp_fused(W, nullptr, X, n, nullptr, Y, H1, H2, H3, stream);
-    mlp_loss(Y, L, n, dY, partial, loss_dst, stream);
-    mlp_backward(W, X, n, H1, H2, H3, dY, dA, dB, G, work, kWork, stream);
-  }
 };
-
-static_assert(kNaWork == flash_mlp::kWork, "the no-allocation gradient splits products like the trainer");
 
 namespace {
 flash_status fail(flash_status s, const std::string& m) { return record_error(s, m); }
@@ -157,17 +141,11 @@ flash_status flash_mlp_create(int64_t max_rows, uint64_t seed, void* hip_stream,
     m->norm = dmalloc<float>(kNorm, m->own);
     m->X = dmalloc<float>(R * kFeat, m->own);
     m->L = dmalloc<float>(R * kOut, m->own);
-    m->H1 = dmalloc<float>(R * kHidden, m->own);
-    m->H2 = dmalloc<float>(R * kHidden, m->own);
-    m->H3 = dmalloc<float>(R * kHidden, m->own);
-    m->dA = dmalloc<float>(R * kHidden, m->own);
-    m->dB = dmalloc<float>(R * kHidden, m->own);
     m->Y = dmalloc<float>(R * kOut, m->own);
-    m->dY = dmalloc<float>(R * kOut, m->own);
     m->loss = dmalloc<float>(1 << 16, m->own);
-    m->partial = dmalloc<double>((3 * R + 255) / 256 + 1, m->own);
+    m->partial = dmalloc<double>(std::max<long>((3 * R + 255) / 256 + 1, kMaxSlabs), m->own);
     m->moments = dmalloc<double>(2 * (kFeat + kOut), m->own);
-    m->work = dmalloc<float>(flash_mlp::kWork, m->own);
+    m->slab = dmalloc<float>(grad_slabs(R) * kSlab, m->own);
     // He-uniform weights (bound sqrt(6 / fan_in)), zero biases
     std::vector<float> w(P, 0.f);
     SplitMix64 rng(seed);
@@ -286,7 +264,7 @@ flash_status flash_mlp_fit_norm(flash_mlp* m, const float* feat, const float* la
 flash_status flash_mlp_forward(flash_mlp* m, const float* x, int64_t n, float* y) {
   if (!m || !x || !y || n < 0) return fail(FLASH_ERR_INVALID_ARG, "null or negative argument");
   try {
-    launch_mlp_fused(m->W, nullptr, x, (long)n, nullptr, y, nullptr, nullptr, nullptr, m->stream);
+    launch_mlp_fused(m->W, nullptr, x, (long)n, nullptr, y, m->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(m->stream));
   } catch (const FlashError& ex) {
@@ -299,9 +277,7 @@ flash_status flash_mlp_grad(flash_mlp* m, const float* x, const float* target, i
   if (!m || !x || !target || !grad || n <= 0) return fail(FLASH_ERR_INVALID_ARG, "null or empty argument");
   if (n > m->max_rows) return fail(FLASH_ERR_CAPACITY, "n exceeds the network's max_rows");
   try {
-    HIPCHK(hipMemcpyAsync(m->X, x, n * kFeat * sizeof(float), hipMemcpyDeviceToDevice, m->stream));
-    HIPCHK(hipMemcpyAsync(m->L, target, n * kOut * sizeof(float), hipMemcpyDeviceToDevice, m->stream));
-    m->grad((long)n, m->loss);
+    launch_mlp_grad(m->W, x, target, (long)n, m->G, m->loss, m->slab, m->partial, m->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(m->stream));
     HIPCHK(hipMemcpy(grad, m->G, MlpLayout::total * sizeof(float), hipMemcpyDeviceToHost));
@@ -322,20 +298,9 @@ flash_status flash_mlp_grad_noalloc(const float* params, const float* x, const f
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     unsigned char* base = noalloc_scratch();
     prepare_mlp();
-    double* partial = reinterpret_cast<double*>(base + kNaOffPartial);
-    float* H1 = reinterpret_cast<float*>(base + kNaOffH);
-    float* H2 = reinterpret_cast<float*>(base + kNaOffH + kNaHid);
-    float* H3 = reinterpret_cast<float*>(base + kNaOffH + 2 * kNaHid);
-    float* dA = reinterpret_cast<float*>(base + kNaOffH + 3 * kNaHid);
-    float* dB = reinterpret_cast<float*>(base + kNaOffH + 4 * kNaHid);
-    float* Y = reinterpret_cast<float*>(base + kNaOffY);
-    float* dY = reinterpret_cast<float*>(base + kNaOffY + kNaOut);
-    float* work = reinterpret_cast<float*>(base + kNaOffWork);
-    // the loss goes to the caller's buffer, or to a slot after the network output when none is given
-    float* loss_dst = loss ? loss : reinterpret_cast<float*>(base + kNaOffY + 2 * kNaOut);
-    launch_mlp_fused(params, nullptr, x, (long)n, nullptr, Y, H1, H2, H3, s);
-    mlp_loss(Y, target, (long)n, dY, partial, loss_dst, s);
-    mlp_backward(params, x, (long)n, H1, H2, H3, dY, dA, dB, grad, work, kNaWork, s);
+    // the loss goes to the caller's buffer, or to the scratch when none is given
+    launch_mlp_grad(params, x, target, (long)n, grad, loss ? loss : reinterpret_cast<float*>(base + kNaOffLoss),
+                    reinterpret_cast<float*>(base + kNaOffSlab), reinterpret_cast<double*>(base + kNaOffPartial), s);
     HIPCHK(hipGetLastError());
   } catch (const FlashError& ex) {
     return fail(ex.st, ex.what());
@@ -362,11 +327,9 @@ flash_status flash_mlp_train(flash_mlp* m, const float* feat, const float* lab, 
       for (int64_t i = 0; i < n; ++i) perm[(size_t)i] = (int)i;
       for (int64_t i = n - 1; i > 0; --i) std::swap(perm[(size_t)i], perm[(size_t)rng.below((uint64_t)i + 1)]);
       HIPCHK(hipMemcpyAsync(idx, perm.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, m->stream));
-      for (long q = 0; q < nb; ++q) {
-        launch_gather_batch(feat, lab, idx + q * batch, batch, m->norm, m->X, m->L, m->stream);
-        m->grad(batch, m->loss + q);
-        launch_adam(m->W, m->G, m->Mo, m->Vo, (int)MlpLayout::total, lr, ++m->adam_t, m->stream);
-      }
+      for (long q = 0; q < nb; ++q)
+        launch_mlp_train(m->W, m->norm, feat, lab, idx + q * batch, batch, m->Mo, m->Vo, lr, ++m->adam_t, m->loss + q,
+                         m->slab, m->partial, m->stream);
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(m->stream));
       HIPCHK(hipMemcpy(lh.data(), m->loss, nb * sizeof(float), hipMemcpyDeviceToHost));
@@ -395,8 +358,8 @@ flash_status flash_mlp_eval(flash_mlp* m, const float* feat, const float* lab, i
       for (long i = 0; i < rows; ++i) id[(size_t)i] = (int)(r0 + i);
       HIPCHK(hipMemcpyAsync(idx, id.data(), rows * sizeof(int), hipMemcpyHostToDevice, m->stream));
       launch_gather_batch(feat, lab, idx, (int)rows, m->norm, m->X, m->L, m->stream);
-      launch_mlp_fused(m->W, nullptr, m->X, rows, nullptr, m->Y, nullptr, nullptr, nullptr, m->stream);
-      mlp_loss(m->Y, m->L, rows, m->dY, m->partial, m->loss, m->stream);
+      launch_mlp_fused(m->W, nullptr, m->X, rows, nullptr, m->Y, m->stream);
+      mlp_loss(m->Y, m->L, rows, m->partial, m->loss, m->stream);
       float l = 0.f;
       HIPCHK(hipStreamSynchronize(m->stream));
       HIPCHK(hipMemcpy(&l, m->loss, sizeof(float), hipMemcpyDeviceToHost));

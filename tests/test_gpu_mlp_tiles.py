@@ -45,3 +45,29 @@ def test_forward_rows_at_tile_edges(n):
     Z = yd.cpu().numpy()[:n].astype(np.float64)
     others = np.arange(n) != n // 2
     assert np.array_equal(Z[others], Y[:n][others])
+
+
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 32897])
+def test_gradient_at_row_blocks(n):
+    """Blocks of 128 rows per workgroup, a partial last one, and more blocks than the grid's 256
+    workgroups (32897 rows: two workgroups take a second block).  Tolerances of test_gpu_mlp.py's
+    gradient test: norm-wise 1e-2 overall, 2e-2 per parameter block."""
+    import torch
+    from paper_2604_17513_amd import flash as F
+    th = _net(6)
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 16)).astype(np.float32)
+    T = rng.standard_normal((n, 3)).astype(np.float32)
+    m = F.Mlp(max_rows=n, seed=0)
+    m.set_params(th)
+    g, loss = m.grad(torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda(), n)
+    L, gr = M.loss_and_grad(th.astype(np.float64), X.astype(np.float64), T.astype(np.float64), rounded=True)
+    print(f"n={n}: loss {loss:.6e} / {L:.6e}, grad {np.linalg.norm(g - gr) / np.linalg.norm(gr):.2e}", flush=True)
+    assert abs(loss - L) <= 2e-3 * L
+    assert np.linalg.norm(g - gr) <= 1e-2 * np.linalg.norm(gr)
+    off = 0
+    for name, shp in M.SHAPES:
+        k = int(np.prod(shp))
+        blk = slice(off, off + k)
+        off += k
+        assert np.linalg.norm(g[blk] - gr[blk]) <= 2e-2 * np.linalg.norm(gr[blk]) + 1e-6 * np.linalg.norm(gr), name
