@@ -44,8 +44,8 @@ struct DevBatch {
   int reuse;                  // reuse capacitance factorisations across Newton iterations
   int lite;                   // 1: fixed-budget lightweight contact update (inertia-only metric)
   int lite_global;            // 1: the lightweight update runs from global memory (k_lite_update)
-  int* lite_done;             // [n_envs] the env's lightweight iteration stopped in this local-global
-                              // iteration (tolerance or budget); its position updates are skipped
+  double* lite_lam;           // [3 per contact] multipliers and world forces after an odd number of updates
+  T* lite_force;              // of a local-global iteration (clam, cforce: after an even number)
   unsigned long long* lite_r; // [n_envs x lg_iterations x (max_newton + 1)] residual of each update of
                               // the step (bits of a non-negative double, combined by atomic maximum)
 

@@ -440,19 +440,19 @@ struct flash_batch {
     }
     if (B.lite_global) {
       // lightweight update from global memory: per local-global iteration the free displacement
-      // z = Gbar b, then alternately u = z + h^2 Gbar H^T lambda (envs still iterating) and one
+      // z = Gbar b, then alternately the product Gbar H^T lambda (envs still iterating) and one
       // update of every vertex group; the last residual evaluation only decides
-      launch(K_CSP, [&] { launch_lite_update<T>(B, mu_d, 0, -1, 0, stream); });
+      launch(K_CSP, [&] { launch_lite_prepare<T>(B, stream); });
       const int N = B.max_newton;
       for (int k = 0; k < p.lg_iterations; ++k) {
         launch(K_PROJECT, [&] { launch_project<T>(B, stream); });
         launch(K_ASSEMBLE, [&] { launch_assemble<T>(B, stream); });
         launch(K_APPLY, [&] { launch_split_apply<T>(B, split, stream); });
-        launch(K_CORRECT, [&] { launch_split_correct<T>(B, split, nullptr, stream); });
         for (int it = 0; it <= N; ++it) {
-          launch(K_CSP, [&] { launch_lite_update<T>(B, mu_d, k, it, k == 0 ? 1 : 0, stream); });
-          if (it < N) launch(K_CORRECT, [&] { launch_split_correct<T>(B, split, B.lite_done, stream); });
+          launch(K_CORRECT, [&] { launch_split_correct<T>(B, split, k, it, stream); });
+          launch(K_CSP, [&] { launch_lite_update<T>(B, split, mu_d, k, it, stream); });
         }
+        launch(K_CSP, [&] { launch_lite_end<T>(B, split, k, stream); });
         if (k == 0 && ws_record) launch(K_MLP, [&] { launch_ws_labels<T>(B, mlp.feat, ws_lab, stream); });
       }
       launch(K_FINALIZE, [&] { launch_finalize<T>(B, mu_d, stream); });
@@ -707,7 +707,7 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
     // in a row: block b always lands on XCD b mod 8, and all envs read it close together in time
     // (envs sharing an inverse then share that XCD's L2 lines).  Slots of blocks an env lacks are
     // padded with empty items (env -1).  The item order never changes the bits.
-    const int tile = split_tile<T>();
+    const int tile = split_tile<T>();   // of the envs that run in chunks
     std::vector<int64_t> poff(ne);
     std::vector<int> nsplit(ne);
     int64_t ptot = 0;
@@ -761,8 +761,6 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
     // empty splits idle: 3 of 8 busy on the 100k-vertex slab's 19.5k contact rows)
     int max_n = 0, max_split = 0;
     for (int e = 0; e < ne; ++e) { max_n = std::max(max_n, H[e].n); max_split = std::max(max_split, nsplit[e]); }
-    const int max_tiles = (max_n + tile - 1) / tile;
-    const int nblk = max_tiles * max_split;
     std::vector<int4> items, titems;
     std::vector<int> tenvs;
     std::vector<int4> chunks;     // (first in tenvs, count, env, 0)
@@ -772,31 +770,35 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
         chunks.push_back(make_int4((int)tenvs.size(), cnt, groups[g][0], 0));
         tenvs.insert(tenvs.end(), groups[g].begin() + c0, groups[g].begin() + c0 + cnt);
       }
-    for (int bg = 0; bg < nblk; bg += kXcds) {
-      for (int e : order) {
-        bool any = false;
-        int4 grp[kXcds];
-        for (int j = 0; j < kXcds; ++j) {
-          const int blk = bg + j, t0 = blk % max_tiles * tile, sp = blk / max_tiles;
-          const bool has = blk < nblk && t0 < H[e].n && sp < nsplit[e];
-          grp[j] = has ? make_int4(e, t0, sp, 0) : make_int4(-1, 0, 0, 0);
-          any = any || has;
+    // Columns per lane of the one-env workgroups.  16 bytes where envs share an inverse (its lines come from
+    // cache, and wide loads need fewer requests: 12 envs of 4096 vertices 4.1 ms per 5 x 10 step, 4.6 with 4
+    // bytes); narrower, with more workgroups and rows in flight, where every line comes from memory: 4 bytes
+    // while splits are of kSplitRows rows (one env of 4096 vertices 1.55 ms, 1.77 with 16 bytes; 40 and 120
+    // distinct envs of up to 1800 vertices 3.1 and 4.6 ms, 3.7 and 5.6 with 16), 8 beyond (9216 and 16384
+    // vertices 4.23 and 10.5 ms; with 4 bytes 4.60 and 11.5, with 16 4.31 and 11.3).
+    int lane_bytes = max_n <= kMaxSplits * kSplitRows ? 4 : 8;
+    for (int e : order)
+      if (groups[group_of[e]].size() > 1) lane_bytes = 16;
+    const int vw = std::max(1, lane_bytes / (int)sizeof(T));
+    // appends the blocks of one list entry per call of `entry`, 8 at a time
+    auto deal = [&](std::vector<int4>& out, size_t count, int width, auto entry) {
+      const int max_tiles = (max_n + width - 1) / width, nblk = max_tiles * max_split;
+      for (int bg = 0; bg < nblk; bg += kXcds)
+        for (size_t q = 0; q < count; ++q) {
+          const int4 id = entry(q);   // (first field, env, last field, of padding items)
+          bool any = false;
+          int4 grp[kXcds];
+          for (int j = 0; j < kXcds; ++j) {
+            const int blk = bg + j, t0 = blk % max_tiles * width, sp = blk / max_tiles;
+            const bool has = blk < nblk && t0 < H[id.y].n && sp < nsplit[id.y];
+            grp[j] = has ? make_int4(id.x, t0, sp, id.z) : make_int4(id.w, 0, 0, 0);
+            any = any || has;
+          }
+          if (any) out.insert(out.end(), grp, grp + kXcds);
         }
-        if (any) items.insert(items.end(), grp, grp + kXcds);
-      }
-      for (const int4& ch : chunks) {
-        const int e = ch.z;
-        bool any = false;
-        int4 grp[kXcds];
-        for (int j = 0; j < kXcds; ++j) {
-          const int blk = bg + j, t0 = blk % max_tiles * tile, sp = blk / max_tiles;
-          const bool has = blk < nblk && t0 < H[e].n && sp < nsplit[e];
-          grp[j] = has ? make_int4(ch.x, t0, sp, ch.y) : make_int4(0, 0, 0, 0);
-          any = any || has;
-        }
-        if (any) titems.insert(titems.end(), grp, grp + kXcds);
-      }
-    }
+    };
+    deal(items, order.size(), 64 * vw, [&](size_t q) { return make_int4(order[q], order[q], 0, -1); });
+    deal(titems, chunks.size(), tile, [&](size_t q) { return make_int4(chunks[q].x, chunks[q].z, chunks[q].y, 0); });
     int4* d_items = items.empty() ? nullptr : dalloc<int4>(items.size(), own);
     if (!items.empty())
       HIPCHK(hipMemcpy(d_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice));
@@ -810,6 +812,8 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
     HIPCHK(hipMemcpy(d_poff, poff.data(), ne * sizeof(int64_t), hipMemcpyHostToDevice));
     b->split.items = d_items;
     b->split.n_items = (int)items.size();
+    b->split.vw = vw;
+    b->split.max_n = max_n;
     b->split.twin_items = d_titems;
     b->split.n_twin_items = (int)titems.size();
     b->split.twin_envs = d_tenvs;
@@ -918,8 +922,8 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
     B.Cm = dalloc<unsigned char>(B.lite_global ? 1 : ne * (rmp * rmp + 16 * rm) * cts + 3 * ne * rm * sizeof(int), own);
   }
   B.base = dalloc<int>(B.lite_global ? 1 : ne * cap, own);
-  B.lite_done = dalloc<int>(ne, own);
-  HIPCHK(hipMemset(B.lite_done, 0, ne * sizeof(int)));
+  B.lite_lam = dalloc<double>(B.lite_global ? 3 * ne * cap : 1, own);
+  B.lite_force = dalloc<T>(B.lite_global ? 3 * ne * cap : 1, own);
   B.lite_r = dalloc<unsigned long long>(B.lite_global ? (size_t)ne * B.lg_iterations * (B.max_newton + 1) : 1, own);
   B.cyf = dalloc<unsigned char>(3 * ne * cap * cts, own);
   B.lust = dalloc<int>(4 * ne, own);

@@ -29,8 +29,8 @@ struct GemvSchedule {
 template <class T> constexpr int gemv_tile(int vw) { return 64 * (int)((8 << vw) / sizeof(T)); }
 
 // Row-split explicit-inverse products of the global-memory lightweight route: each workgroup sums
-// one split of an env's rows (split_rows) for one column tile of 64 x 16 bytes into a partial, and a
-// merge pass adds an env's partials in split order.  The split depends only on the env's own sizes,
+// one split of an env's rows (split_rows) for one column tile into a partial, and whoever reads the product
+// adds an env's partials in split order.  The split depends only on the env's own sizes,
 // so an env gives the same bits alone or in any batch.
 constexpr int kSplitRows = 512;   // rows staged in LDS at a time; the least rows per split
 constexpr int kMaxSplits = 16;    // splits per env beyond which the splits grow instead
@@ -55,6 +55,8 @@ constexpr int kTwinChunk = 8;
 struct SplitSchedule {
   const int4* items;       // (env, first column, split, 0) per workgroup, envs without a twin
   int n_items;
+  int vw;                  // columns per lane of those items' tiles
+  int max_n;               // most vertices of an env
   const int4* twin_items;  // (first env of the chunk in twin_envs, first column, split, envs in the
                            // chunk; 0 pads) per workgroup, envs that share their inverse
   int n_twin_items;
@@ -63,19 +65,23 @@ struct SplitSchedule {
   const int64_t* poff;     // [n_envs] element offset of each env's partials
 };
 template <class T> void launch_split_apply(const DevBatch<T>& B, const SplitSchedule& S, hipStream_t s);
-template <class T> void launch_split_correct(const DevBatch<T>& B, const SplitSchedule& S, const int* skip,
+// Global-memory lightweight iteration.  Product of local-global iteration k's forces after `it` updates, for the
+// envs that have not stopped
+template <class T> void launch_split_correct(const DevBatch<T>& B, const SplitSchedule& S, int k, int it,
                                              hipStream_t s);
+// the warm start's forces, once per step
+template <class T> void launch_lite_prepare(const DevBatch<T>& B, hipStream_t s);
+// residual after `it` updates, and one more update unless the env stops (it = max_newton: residual only)
+template <class T> void launch_lite_update(const DevBatch<T>& B, const SplitSchedule& S, const T* mu_env, int k, int it,
+                                           hipStream_t s);
+// u of every vertex, multipliers and counters of the update each env stopped at
+template <class T> void launch_lite_end(const DevBatch<T>& B, const SplitSchedule& S, int k, hipStream_t s);
 
 template <class T> void launch_apply(const DevBatch<T>& B, const GemvSchedule& S, hipStream_t s);
 template <class T> void launch_csp(const DevBatch<T>& B, const T* mu_env, int first_lg, hipStream_t s);
 // skip (optional): envs with skip[e] != 0 keep their u
 template <class T> void launch_correct(const DevBatch<T>& B, const GemvSchedule& S, hipStream_t s,
                                        const int* skip = nullptr);
-// lightweight update in global memory: it = -1 prepares the warm start's forces (once per step),
-// it >= 0 is the (it + 1)-th residual evaluation of local-global iteration k (an update unless the
-// iteration stops)
-template <class T> void launch_lite_update(const DevBatch<T>& B, const T* mu_env, int k, int it, int first_lg,
-                                           hipStream_t s);
 // The whole local-global loop of a step, one workgroup per env (bitwise equal to the
 // kernel-per-phase sequence project, assemble, apply, csp, correct repeated K times).
 template <class T> void launch_lg_fused(const DevBatch<T>& B, const T* mu_env, hipStream_t s);

@@ -5,10 +5,16 @@
 // of Alg. 1, formed by the explicit-inverse product over the contact rows), evaluates Phi and its
 // generalized-Jacobian blocks at Y = F^T u per contact, and takes lambda <- lambda + delta with
 // (K W~ + E) delta = -Phi per vertex, W~ = h^2 H M^-1 H^T.  The metric couples only the contacts
-// of one vertex, so every vertex group is updated by one thread from global memory; the env's
-// residual is reduced over chunks of contacts first (one launch), then the update decides and
-// updates (a second launch), both spread over (chunks, envs).  The contact displacement follows lambda through
-// the global apply instead of the contact-space Delassus operator, so no cap x cap matrix exists.
+// of one vertex, so every vertex group is updated by one thread from global memory.  The contact displacement
+// follows lambda through the global product instead of the contact-space Delassus operator, so no cap x cap
+// matrix exists.
+//
+// An update is two launches, the product and k_lite_update, because one launch costs about as long as the
+// product's own work on a small batch.  k_lite_update adds up the product's partial sums itself, folds its
+// contacts' residuals into the env's slot of this update, and forms the next multipliers before the env's
+// residual is known: they go to the other of two buffers, and the next product and update leave an env alone
+// whose last residual met the tolerance.  k_lite_end then counts, sums u for every vertex, and brings the
+// multipliers of the update an env stopped at back to the first buffer.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -31,17 +37,14 @@ __device__ __forceinline__ double wg_max(double v, double* sh) {
   return m;
 }
 
-// Residual of contact j at (u, lambda), FP64, at the residual scale s = h^2 / m_v.
+// Residual of contact j at (u of its vertex, lambda lj), FP64, at the residual scale s = h^2 / m_v.
 template <class T, class CT>
-__device__ __forceinline__ double lite_residual(const DevBatch<T>& B, size_t cb, int j, const CT* Fr, int v0, CT mu) {
-  const int NV = B.NV;
-  const CT* F = Fr + 9 * j;
-  const int vi = v0 + B.cvert[cb + j];
-  const double uw0 = (double)B.u[vi], uw1 = (double)B.u[NV + vi], uw2 = (double)B.u[2 * NV + vi];
+__device__ __forceinline__ double lite_residual(const DevBatch<T>& B, size_t cb, int j, const CT* F, const T (&u)[3],
+                                                const double* lj, CT mu) {
+  const double uw0 = (double)u[0], uw1 = (double)u[1], uw2 = (double)u[2];
   double Y[3];
   for (int a = 0; a < 3; ++a) Y[a] = (double)F[3 * a] * uw0 + (double)F[3 * a + 1] * uw1 + (double)F[3 * a + 2] * uw2;
   const double s = (double)B.cs[cb + j];
-  const double* lj = B.clam + 3 * (cb + j);
   const double cnd = B.cd0d[cb + j] + Y[0];
   const double ut1 = Y[1] - (double)B.cdob[2 * (cb + j)], ut2 = Y[2] - (double)B.cdob[2 * (cb + j) + 1];
   const bool att = B.cobs[cb + j] >= kMaxObs;
@@ -62,9 +65,58 @@ __device__ __forceinline__ const CT* lite_frames(const DevBatch<T>& B, size_t cb
   else return B.cframe64 + 9 * cb;
 }
 
+// Multipliers and world forces before (0) and after an odd number of updates of a local-global iteration.
+template <class T>
+__device__ __forceinline__ double* lite_lambda(const DevBatch<T>& B, int it) { return it & 1 ? B.lite_lam : B.clam; }
+template <class T>
+__device__ __forceinline__ T* lite_force(const DevBatch<T>& B, int it) { return it & 1 ? B.lite_force : B.cforce; }
+
+__device__ __forceinline__ int lite_slots(int lg_iterations, int max_newton) { return lg_iterations * (max_newton + 1); }
+
+// Whether env e had stopped by the update of `slot` (its residual met the tolerance; slots of later updates
+// stay zero, so it stays stopped).
+template <class T>
+__device__ __forceinline__ bool lite_stopped(const DevBatch<T>& B, int e, int slot) {
+  const unsigned long long r = B.lite_r[(size_t)e * lite_slots(B.lg_iterations, B.max_newton) + slot];
+  return __longlong_as_double((long long)r) <= B.tol;
+}
+
+// An env's product at a vertex: its row-split partials in split order, kSumBatch loads per component in flight.
+constexpr int kSumBatch = 8;
+template <class T>
+__device__ __forceinline__ void split_sum(const T* P, int ns, int n, int col, T (&s)[3]) {
+  s[0] = s[1] = s[2] = 0;
+  for (int s0 = 0; s0 < ns; s0 += kSumBatch) {
+    T v[kSumBatch][3];
+#pragma unroll
+    for (int q = 0; q < kSumBatch; ++q)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[q][k] = P[((size_t)min(s0 + q, ns - 1) * 3 + k) * n + col];
+#pragma unroll
+    for (int q = 0; q < kSumBatch; ++q)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s[k] = s0 + q < ns ? s[k] + v[q][k] : s[k];
+  }
+}
+// u = z + h^2 s.  The roundings are fixed (components 0 and 2 fused, 1 not), so that both kernels that form u, and
+// any compiler, give the same bits; these are the bits the step has always had.
+template <class T>
+__device__ __forceinline__ T displaced(T z, T hh, T s, int k) {
+#pragma clang fp contract(off)
+  if (k == 1) {
+    const T p = hh * s;
+    return z + p;
+  }
+  return __builtin_elementwise_fma(hh, s, z);
+}
+template <class T>
+__device__ __forceinline__ int split_count(const DevBatch<T>& B, int n, int nrows) {
+  const int R = split_rows(split_cover(n, B.cap));
+  return (nrows + R - 1) / R;
+}
+
 // Once per step, after detection: world forces F lambda of the warm start (the first position
-// update reads them); the env's residual slots cleared; its iteration not stopped.  Grid: (chunks of
-// kBlock contacts, envs).
+// update reads them); the env's residual slots cleared.  Grid: (chunks of kBlock contacts, envs).
 template <class T, class CT>
 __global__ void __launch_bounds__(kBlock) k_lite_prepare(DevBatch<T> B) {
   const int e = blockIdx.y;
@@ -79,85 +131,62 @@ __global__ void __launch_bounds__(kBlock) k_lite_prepare(DevBatch<T> B) {
     for (int k = 0; k < 3; ++k) B.cforce[3 * (cb + j) + k] = (T)(F[k] * l0 + F[3 + k] * l1 + F[6 + k] * l2);
   }
   if (blockIdx.x == 0) {
-    const int ns = B.lg_iterations * (B.max_newton + 1);
+    const int ns = lite_slots(B.lg_iterations, B.max_newton);
     for (int q = threadIdx.x; q < ns; q += kBlock) B.lite_r[(size_t)e * ns + q] = 0ull;
-    if (threadIdx.x == 0) B.lite_done[e] = 0;
   }
 }
 
-// The env's residual at (u, lambda): each workgroup reduces one chunk of kBlock contacts and folds
-// its maximum into the env's slot for this update (non-negative doubles order like their bits, so an
-// integer atomic maximum gives the exact maximum whatever the order).
+// Residual and update `it` of every env that has not stopped; partial: the product's partial sums.  Grid:
+// (chunks of kBlock contacts, envs).  Each workgroup folds its contacts' maximum into the env's slot
+// (non-negative doubles order like their bits, so an integer atomic maximum gives the exact maximum whatever
+// the order); every vertex group whose first contact lies in the chunk takes one update, except with it =
+// max_newton, which only evaluates.  Latency bound (one chain of dependent loads per contact): 7 us for 4104
+// contacts, where the sum of partials, the residual and the update took a launch each, 5 us apiece.
 template <class T, class CT>
-__global__ void __launch_bounds__(kBlock) k_lite_residual(DevBatch<T> B, const T* mu_env, int slot, int it) {
+__global__ void __launch_bounds__(kBlock) k_lite_update(DevBatch<T> B, const T* mu_env, int slot, int it,
+                                                        const T* partial, const int64_t* poff) {
   __shared__ double sh_red[kBlock / 64];
   const int e = blockIdx.y;
-  if (it > 0 && B.lite_done[e]) return;
   const int c = B.ccount[e];
   const int j0 = blockIdx.x * kBlock;
-  if (j0 >= c) return;
+  if (j0 >= c || (it > 0 && lite_stopped(B, e, slot - 1))) return;
   const size_t cb = (size_t)e * B.cap;
   const CT* Fr = lite_frames<T, CT>(B, cb);
   const int v0 = B.voff[e];
+  const int n = B.voff[e + 1] - v0;
   const CT mu = (CT)mu_env[e];
   const int j = j0 + threadIdx.x;
-  const double rloc = j < c ? lite_residual<T, CT>(B, cb, j, Fr, v0, mu) : 0.0;
-  const double r = wg_max(rloc, sh_red);
-  if (threadIdx.x == 0) {
-    const int ns = B.lg_iterations * (B.max_newton + 1);
-    atomicMax(&B.lite_r[(size_t)e * ns + slot], (unsigned long long)__double_as_longlong(r));
-  }
-}
-
-// Decision and update: the env's iteration stops (done flag, counters, not-converged flag) when its
-// residual is at inner_tol or `it` reached the budget; otherwise every vertex group whose first
-// contact lies in this workgroup's chunk takes one update.
-template <class T, class CT>
-__global__ void __launch_bounds__(kBlock) k_lite_apply(DevBatch<T> B, const T* mu_env, int slot, int it, int first_lg) {
-  const int e = blockIdx.y;
-  if (it > 0 && B.lite_done[e]) return;
-  const int c = B.ccount[e];
-  const int ns = B.lg_iterations * (B.max_newton + 1);
-  const double r = __longlong_as_double((long long)B.lite_r[(size_t)e * ns + slot]);
-  const int tid = threadIdx.x;
-  if (r <= B.tol || it >= B.max_newton) {
-    if (blockIdx.x == 0 && tid == 0) {
-      B.lite_done[e] = 1;
-      B.iters[e] += it;
-      if (B.phase) {
-        unsigned long long* cnt = B.phase + (size_t)B.n_envs * 8 + 8 * e;
-        cnt[3] += (r > B.tol) ? 1 : 0;
-        cnt[6] += it;
-        cnt[7] += 1;
-      }
-      if (c > 0 && r > B.tol) B.flags[e] |= 2; else B.flags[e] &= ~2;
-      if (first_lg && B.ws_state) B.ws_state[e] &= ~5;
-    }
-    return;
-  }
-  if (it == 0 && blockIdx.x == 0 && tid == 0) B.lite_done[e] = 0;
-  const int j = blockIdx.x * kBlock + tid;
-  if (j >= c) return;
-  const size_t cb = (size_t)e * B.cap;
   const int* cv = B.cvert + cb;
+  const double* lam_in = lite_lambda(B, it);
+  T u[3] = {0, 0, 0};
+  double rloc = 0.0;
+  if (j < c) {
+    T s[3];
+    split_sum(partial + poff[e], split_count(B, n, c), n, cv[j], s);
+    const T hh = (T)(B.h * B.h);
+    for (int k = 0; k < 3; ++k) u[k] = displaced(B.z[(size_t)k * B.NV + v0 + cv[j]], hh, s[k], k);
+    rloc = lite_residual<T, CT>(B, cb, j, Fr + 9 * j, u, lam_in + 3 * (cb + j), mu);
+  }
+  const double r = wg_max(rloc, sh_red);
+  if (threadIdx.x == 0)
+    atomicMax(&B.lite_r[(size_t)e * lite_slots(B.lg_iterations, B.max_newton) + slot],
+              (unsigned long long)__double_as_longlong(r));
+  if (it >= B.max_newton || j >= c) return;
   if (j > 0 && cv[j - 1] == cv[j]) return;   // not the first contact of its vertex
-  const CT* Fr = lite_frames<T, CT>(B, cb);
+  double* lam_out = lite_lambda(B, it + 1);
+  T* force = lite_force(B, it + 1);
   const int* cobs = B.cobs + cb;
-  const int v0 = B.voff[e];
-  const int NV = B.NV;
-  const CT mu = (CT)mu_env[e];
   const double dmaxf = B.max_force;
   int m = 1;
   while (j + m < c && cv[j + m] == cv[j] && m < kCacheSlots) ++m;
-  const int vi = v0 + cv[j];
-  const CT uw0 = (CT)B.u[vi], uw1 = (CT)B.u[NV + vi], uw2 = (CT)B.u[2 * NV + vi];
+  const CT uw0 = (CT)u[0], uw1 = (CT)u[1], uw2 = (CT)u[2];
   CT Y[3 * kCacheSlots], d0[kCacheSlots], dob[2 * kCacheSlots], dl[3 * kCacheSlots];
   double lam[3 * kCacheSlots];
   for (int q = 0; q < m; ++q) {
     const CT* F = Fr + 9 * (j + q);
     for (int a = 0; a < 3; ++a) {
       Y[3 * q + a] = F[3 * a] * uw0 + F[3 * a + 1] * uw1 + F[3 * a + 2] * uw2;
-      lam[3 * q + a] = B.clam[3 * (cb + j + q) + a];
+      lam[3 * q + a] = lam_in[3 * (cb + j + q) + a];
     }
     d0[q] = (CT)B.cd0[cb + j + q];
     dob[2 * q] = (CT)B.cdob[2 * (cb + j + q)];
@@ -180,23 +209,68 @@ __global__ void __launch_bounds__(kBlock) k_lite_apply(DevBatch<T> B, const T* m
     double ln[3];
     for (int a = 0; a < 3; ++a) {
       ln[a] = fmin(fmax(lam[3 * q + a] + (double)dl[3 * q + a], -dmaxf), dmaxf);
-      B.clam[3 * (cb + j + q) + a] = ln[a];
+      lam_out[3 * (cb + j + q) + a] = ln[a];
     }
     const CT l0 = (CT)ln[0], l1 = (CT)ln[1], l2 = (CT)ln[2];
-    for (int k = 0; k < 3; ++k) B.cforce[3 * (cb + j + q) + k] = (T)(F[k] * l0 + F[3 + k] * l1 + F[6 + k] * l2);
+    for (int k = 0; k < 3; ++k) force[3 * (cb + j + q) + k] = (T)(F[k] * l0 + F[3 + k] * l1 + F[6 + k] * l2);
+  }
+}
+
+// End of a local-global iteration whose updates have the slots from slot0 on: u = z + h^2 Gbar H^T lambda for
+// every vertex, the multipliers and forces of an odd number of updates back in the first buffer, and the
+// counters and flags.  Grid: (chunks of kBlock vertices or contacts, envs).
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_lite_end(DevBatch<T> B, int slot0, int first_lg, const T* partial,
+                                                     const int64_t* poff) {
+  const int e = blockIdx.y;
+  const int c = B.ccount[e];
+  const int v0 = B.voff[e];
+  const int n = B.voff[e + 1] - v0;
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (blockIdx.x * kBlock >= max(n, c)) return;
+  int it = 0;
+  while (it < B.max_newton && !lite_stopped(B, e, slot0 + it)) ++it;
+  if (i < n) {
+    T s[3];
+    split_sum(partial + poff[e], split_count(B, n, c), n, i, s);
+    const T hh = (T)(B.h * B.h);
+    for (int k = 0; k < 3; ++k) {
+      const size_t o = (size_t)k * B.NV + v0 + i;
+      B.u[o] = displaced(B.z[o], hh, s[k], k);
+    }
+  }
+  if ((it & 1) && i < c) {
+    const size_t o = 3 * ((size_t)e * B.cap + i);
+    for (int k = 0; k < 3; ++k) {
+      B.clam[o + k] = B.lite_lam[o + k];
+      B.cforce[o + k] = B.lite_force[o + k];
+    }
+  }
+  if (i == 0) {
+    const bool open = !lite_stopped(B, e, slot0 + it);
+    B.iters[e] += it;
+    if (B.phase) {
+      unsigned long long* cnt = B.phase + (size_t)B.n_envs * 8 + 8 * e;
+      cnt[3] += open ? 1 : 0;
+      cnt[6] += it;
+      cnt[7] += 1;
+    }
+    if (c > 0 && open) B.flags[e] |= 2; else B.flags[e] &= ~2;
+    if (first_lg && B.ws_state) B.ws_state[e] &= ~5;
   }
 }
 
 // Partial sums of one row split of env e's explicit-inverse product for one column tile.
 // ROWS = false: rows 0..n-1 with the right-hand side b (z = Gbar b); ROWS = true: the contact
-// rows with their world forces (u = z + h^2 Gbar H^T lambda).  Gbar is symmetric, so rows are
-// read along their length (16-byte vectors, non-temporal: each row is read once per product).
-template <class T, bool ROWS>
-__global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4* items, const int* skip,
+// rows with their world forces (Gbar H^T lambda).  Gbar is symmetric, so rows are
+// read along their length (VW columns per lane, non-temporal: each row is read once per product).
+// Few envs are bound by latency, not bandwidth: a wave reads its 128 rows of a split in batches of UNROLL, two
+// batches in flight.  One env of 4096 vertices (128 workgroups of 16-byte lanes): 25 us at 4 rows a batch, 15 us
+// with 4-byte lanes (four times the workgroups) and 16 rows.
+template <class T, bool ROWS, int VW, int UNROLL>
+__global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4* items, const T* force, int slot,
                                                        T* partial, const int64_t* poff) {
-  constexpr int VW = (int)(16 / sizeof(T));
   constexpr int TILE = 64 * VW;
-  constexpr int UNROLL = 4;
   constexpr int WS = kBlock / 64;
   typedef T vec_t __attribute__((ext_vector_type(VW)));
   typedef T f4_t __attribute__((ext_vector_type(4)));
@@ -205,7 +279,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4
   __shared__ T s_red[(WS - 1) * 3 * TILE];
   const int4 item = items[blockIdx.x];
   const int e = item.x, tile0 = item.y, split = item.z;
-  if (e < 0 || (skip && skip[e])) return;   // padding item, or an env whose iteration stopped
+  if (e < 0 || (slot >= 0 && lite_stopped(B, e, slot))) return;   // padding item, or an env that has stopped
   const int v0 = B.voff[e];
   const int n = B.voff[e + 1] - v0;
   const int ld = B.gld[e];
@@ -228,7 +302,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4
     if (ROWS) {
       const size_t j = (size_t)e * B.cap + c0 + r;
       s_row[r] = B.cvert[j];
-      f[0] = B.cforce[3 * j]; f[1] = B.cforce[3 * j + 1]; f[2] = B.cforce[3 * j + 2];
+      f[0] = force[3 * j]; f[1] = force[3 * j + 1]; f[2] = force[3 * j + 2];
     } else {
       s_row[r] = c0 + r;
       f[0] = B.b[v0 + c0 + r]; f[1] = B.b[B.NV + v0 + c0 + r]; f[2] = B.b[2 * B.NV + v0 + c0 + r];
@@ -303,7 +377,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4
 constexpr int kTwinRows = 128;
 template <class T, bool ROWS>
 __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, const int4* items, const int* envs,
-                                                             const int* skip, T* partial, const int64_t* poff) {
+                                                             const T* force, int slot, T* partial, const int64_t* poff) {
   constexpr int VW = (int)(16 / sizeof(T));
   constexpr int TILE = 64 * VW;
   constexpr int UNROLL = 4;
@@ -337,7 +411,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
     if ((int)threadIdx.x < w) {
       e = envs[item.x + threadIdx.x];
       const int nrows = ROWS ? B.ccount[e] : n;
-      if (!(skip && skip[e]) && r0 < nrows) r1 = min(r0 + R, nrows);
+      if (!(slot >= 0 && lite_stopped(B, e, slot)) && r0 < nrows) r1 = min(r0 + R, nrows);
     }
     s_e[threadIdx.x] = e;
     s_r1[threadIdx.x] = r1;
@@ -369,7 +443,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
         if (ROWS) {
           const size_t j = (size_t)e * B.cap + c0 + r;
           row = B.cvert[j];
-          f[0] = B.cforce[3 * j]; f[1] = B.cforce[3 * j + 1]; f[2] = B.cforce[3 * j + 2];
+          f[0] = force[3 * j]; f[1] = force[3 * j + 1]; f[2] = force[3 * j + 2];
         } else {
           const int vb = B.voff[e] + c0 + r;
           row = c0 + r;
@@ -483,82 +557,82 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
   }
 }
 
-// Adds each env's row-split partials in split order: z = sum (ROWS = false) or u = z + h^2 sum.
-template <class T, bool ROWS>
-__global__ void __launch_bounds__(kBlock) k_gemv_merge(DevBatch<T> B, const int* skip, const T* partial,
-                                                       const int64_t* poff) {
+// Adds each env's row-split partials in split order: z = sum.
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_gemv_merge(DevBatch<T> B, const T* partial, const int64_t* poff) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= B.NV) return;
   const int e = B.vert_env[i];
-  if (skip && skip[e]) return;
   const int v0 = B.voff[e];
-  const int n = B.voff[e + 1] - v0, col = i - v0;
-  const int nrows = ROWS ? B.ccount[e] : n;
-  const int R = split_rows(split_cover(n, B.cap));
-  const int ns = (nrows + R - 1) / R;
-  const T* P = partial + poff[e];
-  const T hh = (T)(B.h * B.h);
-  for (int k = 0; k < 3; ++k) {
-    T s = 0;
-    for (int sp = 0; sp < ns; ++sp) s += P[((size_t)sp * 3 + k) * n + col];
-    const size_t o = (size_t)k * B.NV + i;
-    if (ROWS) B.u[o] = B.z[o] + hh * s;
-    else B.z[o] = s;
+  const int n = B.voff[e + 1] - v0;
+  T s[3];
+  split_sum(partial + poff[e], split_count(B, n, n), n, i - v0, s);
+  for (int k = 0; k < 3; ++k) B.z[(size_t)k * B.NV + i] = s[k];
+}
+
+template <class T, bool ROWS>
+void launch_split_product(const DevBatch<T>& B, const SplitSchedule& S, const T* force, int slot, hipStream_t s) {
+  T* P = static_cast<T*>(S.partial);
+  if (S.n_items > 0) {
+    const dim3 g((unsigned)S.n_items), blk(kBlock);
+    constexpr int V16 = (int)(16 / sizeof(T)), V8 = (int)(8 / sizeof(T));
+    if (S.vw == V16)
+      hipLaunchKernelGGL((k_gemv_split<T, ROWS, V16, 8>), g, blk, 0, s, B, S.items, force, slot, P, S.poff);
+    else if (S.vw == V8)
+      hipLaunchKernelGGL((k_gemv_split<T, ROWS, V8, 16>), g, blk, 0, s, B, S.items, force, slot, P, S.poff);
+    else
+      hipLaunchKernelGGL((k_gemv_split<T, ROWS, 1, 16>), g, blk, 0, s, B, S.items, force, slot, P, S.poff);
   }
+  if (S.n_twin_items > 0)
+    hipLaunchKernelGGL((k_gemv_split_twins<T, ROWS>), dim3((unsigned)S.n_twin_items), dim3(kBlock), 0, s, B,
+                       S.twin_items, S.twin_envs, force, slot, P, S.poff);
 }
 
 }  // namespace
 
 template <class T>
 void launch_split_apply(const DevBatch<T>& B, const SplitSchedule& S, hipStream_t s) {
-  T* P = static_cast<T*>(S.partial);
-  if (S.n_items > 0)
-    hipLaunchKernelGGL((k_gemv_split<T, false>), dim3((unsigned)S.n_items), dim3(kBlock), 0, s, B, S.items,
-                       (const int*)nullptr, P, S.poff);
-  if (S.n_twin_items > 0)
-    hipLaunchKernelGGL((k_gemv_split_twins<T, false>), dim3((unsigned)S.n_twin_items), dim3(kBlock), 0, s, B,
-                       S.twin_items, S.twin_envs, (const int*)nullptr, P, S.poff);
-  hipLaunchKernelGGL((k_gemv_merge<T, false>), dim3((unsigned)((B.NV + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, B,
-                     (const int*)nullptr, (const T*)P, S.poff);
+  launch_split_product<T, false>(B, S, nullptr, -1, s);
+  hipLaunchKernelGGL(k_gemv_merge<T>, dim3((unsigned)((B.NV + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, B,
+                     (const T*)S.partial, S.poff);
 }
 
 template <class T>
-void launch_split_correct(const DevBatch<T>& B, const SplitSchedule& S, const int* skip, hipStream_t s) {
-  T* P = static_cast<T*>(S.partial);
-  if (S.n_items > 0)
-    hipLaunchKernelGGL((k_gemv_split<T, true>), dim3((unsigned)S.n_items), dim3(kBlock), 0, s, B, S.items, skip, P,
-                       S.poff);
-  if (S.n_twin_items > 0)
-    hipLaunchKernelGGL((k_gemv_split_twins<T, true>), dim3((unsigned)S.n_twin_items), dim3(kBlock), 0, s, B,
-                       S.twin_items, S.twin_envs, skip, P, S.poff);
-  hipLaunchKernelGGL((k_gemv_merge<T, true>), dim3((unsigned)((B.NV + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, B,
-                     skip, (const T*)P, S.poff);
+void launch_split_correct(const DevBatch<T>& B, const SplitSchedule& S, int k, int it, hipStream_t s) {
+  launch_split_product<T, true>(B, S, it & 1 ? B.lite_force : B.cforce, it > 0 ? k * (B.max_newton + 1) + it - 1 : -1, s);
 }
 
-template void launch_split_apply<float>(const DevBatch<float>&, const SplitSchedule&, hipStream_t);
-template void launch_split_apply<double>(const DevBatch<double>&, const SplitSchedule&, hipStream_t);
-template void launch_split_correct<float>(const DevBatch<float>&, const SplitSchedule&, const int*, hipStream_t);
-template void launch_split_correct<double>(const DevBatch<double>&, const SplitSchedule&, const int*, hipStream_t);
-
 template <class T>
-void launch_lite_update(const DevBatch<T>& B, const T* mu_env, int k, int it, int first_lg, hipStream_t s) {
+void launch_lite_prepare(const DevBatch<T>& B, hipStream_t s) {
   const dim3 g((unsigned)((B.cap + kBlock - 1) / kBlock), (unsigned)B.n_envs), blk(kBlock);
-  if (it < 0) {
-    if (B.csp64) hipLaunchKernelGGL((k_lite_prepare<T, double>), g, blk, 0, s, B);
-    else hipLaunchKernelGGL((k_lite_prepare<T, T>), g, blk, 0, s, B);
-    return;
-  }
-  const int slot = k * (B.max_newton + 1) + it;
-  if (B.csp64) {
-    hipLaunchKernelGGL((k_lite_residual<T, double>), g, blk, 0, s, B, mu_env, slot, it);
-    hipLaunchKernelGGL((k_lite_apply<T, double>), g, blk, 0, s, B, mu_env, slot, it, first_lg);
-  } else {
-    hipLaunchKernelGGL((k_lite_residual<T, T>), g, blk, 0, s, B, mu_env, slot, it);
-    hipLaunchKernelGGL((k_lite_apply<T, T>), g, blk, 0, s, B, mu_env, slot, it, first_lg);
-  }
+  if (B.csp64) hipLaunchKernelGGL((k_lite_prepare<T, double>), g, blk, 0, s, B);
+  else hipLaunchKernelGGL((k_lite_prepare<T, T>), g, blk, 0, s, B);
 }
 
-template void launch_lite_update<float>(const DevBatch<float>&, const float*, int, int, int, hipStream_t);
-template void launch_lite_update<double>(const DevBatch<double>&, const double*, int, int, int, hipStream_t);
+template <class T>
+void launch_lite_update(const DevBatch<T>& B, const SplitSchedule& S, const T* mu_env, int k, int it, hipStream_t s) {
+  const dim3 g((unsigned)((B.cap + kBlock - 1) / kBlock), (unsigned)B.n_envs), blk(kBlock);
+  const int slot = k * (B.max_newton + 1) + it;
+  const T* P = static_cast<const T*>(S.partial);
+  if (B.csp64) hipLaunchKernelGGL((k_lite_update<T, double>), g, blk, 0, s, B, mu_env, slot, it, P, S.poff);
+  else hipLaunchKernelGGL((k_lite_update<T, T>), g, blk, 0, s, B, mu_env, slot, it, P, S.poff);
+}
+
+template <class T>
+void launch_lite_end(const DevBatch<T>& B, const SplitSchedule& S, int k, hipStream_t s) {
+  const int most = S.max_n > B.cap ? S.max_n : B.cap;
+  hipLaunchKernelGGL(k_lite_end<T>, dim3((unsigned)((most + kBlock - 1) / kBlock), (unsigned)B.n_envs), dim3(kBlock), 0,
+                     s, B, k * (B.max_newton + 1), k == 0 ? 1 : 0, (const T*)S.partial, S.poff);
+}
+
+#define FLASH_LITE(T)                                                                                              \
+  template void launch_split_apply<T>(const DevBatch<T>&, const SplitSchedule&, hipStream_t);                      \
+  template void launch_split_correct<T>(const DevBatch<T>&, const SplitSchedule&, int, int, hipStream_t);          \
+  template void launch_lite_prepare<T>(const DevBatch<T>&, hipStream_t);                                           \
+  template void launch_lite_update<T>(const DevBatch<T>&, const SplitSchedule&, const T*, int, int, hipStream_t);  \
+  template void launch_lite_end<T>(const DevBatch<T>&, const SplitSchedule&, int, hipStream_t);
+FLASH_LITE(float)
+FLASH_LITE(double)
+#undef FLASH_LITE
 
 }  // namespace flash
