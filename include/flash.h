@@ -185,8 +185,8 @@ typedef struct {
                                      explicit inverse (same mesh and material) run the inverse
                                      products in chunks of this many envs per workgroup, so that
                                      each inverse row read serves the whole chunk.  0 (default):
-                                     automatic (8, else 4, while each product keeps at least 512
-                                     workgroups, else 1); 1: one env per workgroup; 2..8: that many.
+                                     automatic (16 in FP32, else 8, else 4, while each product
+                                     keeps at least 512 workgroups, else 1); 1: one env per workgroup; 2..8: that many.
                                      Every choice gives the same bits. */
 } flash_params;
 

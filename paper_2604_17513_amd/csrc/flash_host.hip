@@ -727,12 +727,11 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
       if (H[e].twin < 0) { group_of[e] = (int)groups.size(); groups.push_back({e}); }
       else groups[group_of[H[e].twin]].push_back(e);
     }
-    // A group's chunk size is twin_chunk, or by default 8, else 4, whichever still leaves
+    // A group's chunk size is twin_chunk, or by default 16 (FP32), else 8, else 4, whichever still leaves
     // kMinTwinItems workgroups per product (fewer, longer workgroups leave CUs idle), else one env
-    // per workgroup.  Measured with the first version of the chunk kernel on the 64 x 64 folding
-    // sheet (5 x 10 budget, ms per step at chunk 1 / 4 / 8): 8 envs 3.8 / 5.4 / 7.4, 16 envs
-    // 6.2 / 5.7 / 7.5, 32 envs 10.0 / 9.5 / 7.8, 256 envs 60.2 / 52.4 / 43.2; chunks of 2 were
-    // slower than 1 at every size.
+    // per workgroup.  Measured on the 64 x 64 folding sheet (5 x 10 budget, ms per step, FP32): 8 envs 3.2 in
+    // chunks of 4; 32 envs 4.8 and 64 envs 7.0 in chunks of 8 and 16 on the matrix cores, 6.6 and 11.8 in
+    // chunks of 8 with vector arithmetic; 256 envs 25.8, 33.6 with vector arithmetic.
     constexpr int kMinTwinItems = 512;
     std::vector<int> order;       // envs run one per workgroup, largest first
     std::vector<int> gorder;      // twin groups run in chunks, largest envs first
@@ -744,8 +743,8 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
       if (b->p.twin_chunk > 0) {
         c = std::min(b->p.twin_chunk, m);
       } else {
-        for (const int cand : {kTwinChunk, 4})
-          if (m >= cand && (int64_t)((m + cand - 1) / cand) * per_env >= kMinTwinItems) { c = cand; break; }
+        for (const int cand : {kWideChunk, kTwinChunk, 4})
+          if ((cand <= kTwinChunk || sizeof(T) == 4) && m >= cand && (int64_t)((m + cand - 1) / cand) * per_env >= kMinTwinItems) { c = cand; break; }
       }
       gchunk[g] = c;
       if (c == 1) order.insert(order.end(), groups[g].begin(), groups[g].end());
@@ -817,6 +816,8 @@ void build_device(flash_batch* b, std::vector<HostEnv>& H, const flash_env_desc*
     b->split.twin_items = d_titems;
     b->split.n_twin_items = (int)titems.size();
     b->split.twin_envs = d_tenvs;
+    b->split.max_chunk = 1;
+    for (int g : gorder) b->split.max_chunk = std::max(b->split.max_chunk, gchunk[g]);
     b->split.partial = dalloc<T>((size_t)ptot, own);
     b->split.poff = d_poff;
   }
@@ -1401,6 +1402,7 @@ flash_status flash_create_batch(const flash_env_desc* envs, int32_t n_envs, cons
     size_t static_lds = 0;
     if (b->fp64) HIPCHK(prepare_csp<double>(&static_lds));
     else HIPCHK(prepare_csp<float>(&static_lds));
+    if (!b->fp64 && b->bf.lite_global) HIPCHK(prepare_lite());
     if (static_lds > kCspStaticLds)
       throw FlashError(FLASH_ERR_DEVICE, "contact-solve kernels use " + std::to_string(static_lds) +
                                              " bytes of static LDS, above the " + std::to_string(kCspStaticLds) +

@@ -51,7 +51,8 @@ __host__ __device__ inline int split_cover(int n, int cap) {
 }
 // Envs that share one inverse (identical mesh and material) run their split products in chunks of
 // up to kTwinChunk envs per workgroup: each inverse row vector loaded serves the whole chunk.
-constexpr int kTwinChunk = 8;
+constexpr int kTwinChunk = 8;    // in FP64, and the most that twin_chunk may ask for
+constexpr int kWideChunk = 16;   // in FP32 by default: 48 right-hand sides fill three matrix-core tiles
 struct SplitSchedule {
   const int4* items;       // (env, first column, split, 0) per workgroup, envs without a twin
   int n_items;
@@ -60,11 +61,14 @@ struct SplitSchedule {
   const int4* twin_items;  // (first env of the chunk in twin_envs, first column, split, envs in the
                            // chunk; 0 pads) per workgroup, envs that share their inverse
   int n_twin_items;
+  int max_chunk;           // most envs of a chunk
   const int* twin_envs;    // chunks of envs sharing one inverse, in batch order within a group
   void* partial;           // T [sum over envs of splits x 3 x n]
   const int64_t* poff;     // [n_envs] element offset of each env's partials
 };
 template <class T> void launch_split_apply(const DevBatch<T>& B, const SplitSchedule& S, hipStream_t s);
+// Raises the dynamic LDS limit of the chunk products (before their first launch); the first error.
+hipError_t prepare_lite();
 // Global-memory lightweight iteration.  Product of local-global iteration k's forces after `it` updates, for the
 // envs that have not stopped
 template <class T> void launch_split_correct(const DevBatch<T>& B, const SplitSchedule& S, int k, int it,

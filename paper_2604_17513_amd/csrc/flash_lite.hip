@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "flash_contact.h"
 #include "flash_device.h"
@@ -376,8 +377,8 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split(DevBatch<T> B, const int4
 // FP32, 2 in FP64).
 constexpr int kTwinRows = 128;
 template <class T, bool ROWS>
-__global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, const int4* items, const int* envs,
-                                                             const T* force, int slot, T* partial, const int64_t* poff) {
+__device__ __forceinline__ void twins_vector(const DevBatch<T>& B, const int* envs, int w, int tile0, int split,
+                                             const T* force, int slot, T* partial, const int64_t* poff) {
   constexpr int VW = (int)(16 / sizeof(T));
   constexpr int TILE = 64 * VW;
   constexpr int UNROLL = 4;
@@ -398,10 +399,8 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
   __shared__ int s_mixed;           // some position has envs reading different rows
   __shared__ T s_red[(WS - 1) * 3 * TILE];
   __shared__ int s_e[EB], s_r1[EB];
-  const int4 item = items[blockIdx.x];
-  if (item.w <= 0) return;   // padding item
-  const int tile0 = item.y, split = item.z, w = item.w;
-  const int e0 = envs[item.x];
+  __syncthreads();   // the LDS may still be read for the workgroup's previous envs
+  const int e0 = envs[0];
   const int n = B.voff[e0 + 1] - B.voff[e0];   // the same mesh, inverse and split size for the chunk
   const int ld = B.gld[e0];
   const int R = split_rows(split_cover(n, B.cap));
@@ -409,7 +408,7 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
   if (threadIdx.x < EB) {
     int e = -1, r1 = r0;
     if ((int)threadIdx.x < w) {
-      e = envs[item.x + threadIdx.x];
+      e = envs[threadIdx.x];
       const int nrows = ROWS ? B.ccount[e] : n;
       if (!(slot >= 0 && lite_stopped(B, e, slot)) && r0 < nrows) r1 = min(r0 + R, nrows);
     }
@@ -557,6 +556,197 @@ __global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, cons
   }
 }
 
+template <class T, bool ROWS>
+__global__ void __launch_bounds__(kBlock) k_gemv_split_twins(DevBatch<T> B, const int4* items, const int* envs,
+                                                             const T* force, int slot, T* partial, const int64_t* poff) {
+  const int4 item = items[blockIdx.x];
+  if (item.w > 0) twins_vector<T, ROWS>(B, envs + item.x, item.w, item.y, item.z, force, slot, partial, poff);
+}
+
+// The FP32 products of a chunk of up to kWideChunk envs on the matrix cores: NT tiles of 16 columns hold the
+// chunk's 3 right-hand sides per env, the left operand is the inverse (16 of its columns, 4 of a wave's rows per
+// instruction).  v_mfma_f32_16x16x4_f32 adds its four products as a chain of FMAs in row order, and a wave takes
+// its rows in k_gemv_split's order, so every env gets k_gemv_split's bits.  Bound by the matrix cores (140 TFLOP/s
+// measured for this instruction; a wave's inverse rows are loaded three steps ahead, the next block's right-hand
+// sides during the products): 256 sheets of 4096 vertices 330 us a product, 25 of a workgroup's 39 us in the
+// products, the rest before the first and in the sum over the waves; the vector form took 456 us.
+// Where the envs of a chunk read different rows somewhere in the split, the vector form takes the whole split.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int kWideTile = 256;                              // columns of a workgroup
+constexpr int kWideRows = 128;                              // rows staged at a time
+constexpr int kWideRed = 65;                                // padded rows of the reduction area
+constexpr int wide_stride(int nt) { return 16 * nt + 4; }   // a wave's rows, 4 apart, fall on different banks
+constexpr size_t wide_smem(int nt) {
+  const int rhs = 2 * kWideRows * wide_stride(nt), red = kBlock / 64 * kWideTile / 16 * 4 * kWideRed;
+  return sizeof(float) * (rhs > red ? rhs : red);
+}
+template <bool ROWS, int NT>
+__global__ void __launch_bounds__(kBlock) k_gemv_split_wide(DevBatch<float> B, const int4* items, const int* envs,
+                                                            const float* force, int slot, float* partial,
+                                                            const int64_t* poff) {
+  constexpr int WS = kBlock / 64, SR = kWideRows, TILE = kWideTile;
+  constexpr int BS = wide_stride(NT);
+  constexpr int CT = TILE / 16;     // column tiles of a wave
+  constexpr int RS = kWideRed;
+  constexpr int NB = 4;             // steps whose inverse rows are in flight or in use
+  constexpr int EB = kWideChunk * SR / kBlock;   // envs whose right-hand side a thread stages, one row each
+  static_assert(SR % (4 * WS * NB) == 0 && kBlock % SR == 0, "staging and steps cover whole blocks");
+  extern __shared__ __align__(16) float s_buf[];   // two blocks of right-hand sides [row][BS], then the reduction
+  __shared__ int s_one[2][SR];                     // and the rows they multiply
+  __shared__ int s_mixed;
+  __shared__ int s_e[kWideChunk], s_r1[kWideChunk];
+  __shared__ int64_t s_off[kWideChunk];
+  const int4 item = items[blockIdx.x];
+  const int w = item.w, tile0 = item.y, split = item.z;
+  if (w <= 0) return;   // padding item
+  const int* chunk = envs + item.x;
+  const int e0 = chunk[0];
+  const int n = B.voff[e0 + 1] - B.voff[e0];   // the same mesh, inverse and split size for the chunk
+  const int ld = B.gld[e0];
+  const int R = split_rows(split_cover(n, B.cap));
+  const int r0 = split * R;
+  const int tid = threadIdx.x;
+  if (tid < kWideChunk) {
+    const int e = chunk[min(tid, w - 1)];
+    int r1 = r0;
+    if (tid < w) {
+      const int nrows = ROWS ? B.ccount[e] : n;
+      if (!(slot >= 0 && lite_stopped(B, e, slot)) && r0 < nrows) r1 = min(r0 + R, nrows);
+    }
+    s_e[tid] = e;
+    s_r1[tid] = r1;
+    s_off[tid] = poff[e] + (int64_t)split * 3 * n;
+  }
+  if (tid == 0) s_mixed = 0;
+  for (int r = tid; r < 2 * SR; r += kBlock)   // columns past the chunk's stay zero
+    for (int q = 3 * w; q < 16 * NT; ++q) s_buf[r * BS + q] = 0.f;
+  __syncthreads();
+  int r1m = r0, el = e0;   // the most rows an env of the chunk reads, and such an env
+  for (int t = 0; t < w; ++t)
+    if (s_r1[t] > r1m) { r1m = s_r1[t]; el = s_e[t]; }
+  if (r1m == r0) return;   // no env of the chunk reads rows in this split (uniform over the block)
+  if (ROWS) {
+    // does every env that reads at a position read that env's row?
+    bool same = true;
+    for (int p = r0 + tid; p < r1m; p += kBlock) {
+      const int one = B.cvert[(size_t)el * B.cap + p];
+#pragma unroll
+      for (int t = 0; t < kWideChunk; ++t)   // (past the chunk: its last env, reading nothing)
+        same &= (B.cvert[(size_t)s_e[t] * B.cap + min(p, max(s_r1[t] - 1, 0))] == one) | (p >= s_r1[t]);
+    }
+    if (!same) s_mixed = 1;
+    __syncthreads();
+    if (s_mixed) {
+      for (int t = 0; t < w; t += kTwinChunk)
+        twins_vector<float, ROWS>(B, chunk + t, min(kTwinChunk, w - t), tile0, split, force, slot, partial, poff);
+      return;
+    }
+  }
+  const float* G = B.G + B.goff[e0];
+  const int l = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lm = l & 15, lk = l >> 4;
+  const float* Gl[4];   // this lane's four columns of each 64 (past the row: its last four, not stored)
+#pragma unroll
+  for (int c = 0; c < 4; ++c) Gl[c] = G + min(tile0 + 64 * c + 4 * lm, ld - 4);
+  // a block's right-hand sides and rows: to registers, and from there to LDS once the block before is done
+  const int sr = tid % SR, st = tid / SR * EB;
+  float f[EB][3];
+  int one = 0;
+  auto fetch = [&](int c0) {
+    const int p = c0 + sr;
+    if (ROWS) one = B.cvert[(size_t)el * B.cap + min(p, r1m - 1)];
+    else one = min(p, r1m - 1);
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      const int e = s_e[st + i], q = min(p, max(s_r1[st + i] - 1, 0));
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        f[i][k] = ROWS ? force[3 * ((size_t)e * B.cap + q) + k] : B.b[(size_t)k * B.NV + B.voff[e] + q];
+    }
+  };
+  auto stage = [&](int c0, int buf) {
+    if (tid < SR) s_one[buf][sr] = one;
+#pragma unroll
+    for (int i = 0; i < EB; ++i)
+      if (st + i < w) {
+        const bool reads = c0 + sr < s_r1[st + i];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s_buf[(buf * SR + sr) * BS + 3 * (st + i) + k] = reads ? f[i][k] : 0.f;
+      }
+  };
+  floatx4 acc[CT][NT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[c][t] = floatx4{};
+  const int rl = wave + WS * lk;   // this lane's row of a step
+  fetch(r0);
+  for (int c0 = r0, buf = 0; c0 < r1m; c0 += SR, buf ^= 1) {
+    stage(c0, buf);
+    __syncthreads();
+    if (c0 + SR < r1m) fetch(c0 + SR);
+    __builtin_amdgcn_sched_barrier(0);
+    // whole rounds of NB steps: rows past the last have zero right-hand sides
+    const int steps = (min(SR, r1m - c0) + 4 * WS * NB - 1) / (4 * WS * NB) * NB;
+    const int* rows = s_one[buf] + rl;
+    const float* rhs = s_buf + (buf * SR + rl) * BS + lm;
+    auto load = [&](int i, floatx4 (&a)[4]) {
+      const size_t o = (size_t)rows[min(i, steps - 1) * 4 * WS] * ld;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a[c] = *reinterpret_cast<const floatx4*>(Gl[c] + o);
+    };
+    floatx4 an[NB][4];
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      load(p, an[p]);
+      __builtin_amdgcn_sched_barrier(0);   // in the order of their use, so that the first wait is for the first only
+    }
+#pragma unroll 1
+    for (int i = 0; i < steps; i += NB)
+#pragma unroll
+      for (int p = 0; p < NB; ++p) {
+        float b[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) b[t] = rhs[(i + p) * 4 * WS * BS + 16 * t];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+              acc[4 * c + q][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(an[p][c][q], b[t], acc[4 * c + q][t], 0, 0, 0);
+        load(i + p + NB, an[p]);
+        __builtin_amdgcn_sched_barrier(0);   // the loads stay NB - 1 steps ahead of their use
+      }
+  }
+  // k_gemv_split's fixed-order sum over the waves, one tile of right-hand sides at a time.  Tile 4 c + q,
+  // register r, lane lm + 16 g hold column 64 c + 16 g + 4 r + q of right-hand side lm.
+  const int at = ((l & 3) * 4 + ((l >> 2) & 3)) * RS + 16 * (l >> 4);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_buf[((wave * CT + c) * 4 + r) * RS + l] = acc[c][t][r];
+    __syncthreads();
+#pragma unroll 1
+    for (int j = wave; j < 16; j += WS) {   // a right-hand side per wave and turn
+      const int en = (16 * t + j) / 3, k = 16 * t + j - 3 * en;
+      if (en >= w || s_r1[en] <= r0) continue;
+      float* P = partial + s_off[en] + (int64_t)k * n + tile0 + l;
+      float v[4][WS];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int u = 0; u < WS; ++u) v[c][u] = s_buf[(u * CT + 4 * c) * 4 * RS + at + j];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (tile0 + 64 * c + l < n) P[64 * c] = ((v[c][0] + v[c][1]) + v[c][2]) + v[c][3];
+    }
+  }
+}
+
 // Adds each env's row-split partials in split order: z = sum.
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_gemv_merge(DevBatch<T> B, const T* partial, const int64_t* poff) {
@@ -583,12 +773,36 @@ void launch_split_product(const DevBatch<T>& B, const SplitSchedule& S, const T*
     else
       hipLaunchKernelGGL((k_gemv_split<T, ROWS, 1, 16>), g, blk, 0, s, B, S.items, force, slot, P, S.poff);
   }
-  if (S.n_twin_items > 0)
-    hipLaunchKernelGGL((k_gemv_split_twins<T, ROWS>), dim3((unsigned)S.n_twin_items), dim3(kBlock), 0, s, B,
-                       S.twin_items, S.twin_envs, force, slot, P, S.poff);
+  if (S.n_twin_items > 0) {
+    const dim3 g((unsigned)S.n_twin_items), blk(kBlock);
+    if constexpr (std::is_same<T, float>::value) {
+      auto go = [&](auto kernel, int nt) {
+        hipLaunchKernelGGL(kernel, g, blk, wide_smem(nt), s, B, S.twin_items, S.twin_envs, force, slot, P, S.poff);
+      };
+      if (3 * S.max_chunk <= 16) go(k_gemv_split_wide<ROWS, 1>, 1);
+      else if (3 * S.max_chunk <= 32) go(k_gemv_split_wide<ROWS, 2>, 2);
+      else go(k_gemv_split_wide<ROWS, 3>, 3);
+    } else {
+      hipLaunchKernelGGL((k_gemv_split_twins<T, ROWS>), g, blk, 0, s, B, S.twin_items, S.twin_envs, force, slot, P,
+                         S.poff);
+    }
+  }
 }
 
 }  // namespace
+
+hipError_t prepare_lite() {
+  const std::pair<const void*, int> kernels[] = {
+      {(const void*)k_gemv_split_wide<false, 1>, 1}, {(const void*)k_gemv_split_wide<true, 1>, 1},
+      {(const void*)k_gemv_split_wide<false, 2>, 2}, {(const void*)k_gemv_split_wide<true, 2>, 2},
+      {(const void*)k_gemv_split_wide<false, 3>, 3}, {(const void*)k_gemv_split_wide<true, 3>, 3}};
+  hipError_t st = hipSuccess;
+  for (const auto& k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_smem(k.second));
+    if (st == hipSuccess) st = e;
+  }
+  return st;
+}
 
 template <class T>
 void launch_split_apply(const DevBatch<T>& B, const SplitSchedule& S, hipStream_t s) {
