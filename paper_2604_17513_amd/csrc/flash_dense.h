@@ -388,6 +388,63 @@ __device__ __forceinline__ void lu_panel(T* A, int ld, int k0, int kb, int m, ld
     if (pos[q] >= 0) perm[k0 + pos[q]] = row[q];
 }
 
+// The value of a lane that is the same for the whole wave.
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const int2 v = __builtin_bit_cast(int2, x);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(v.x, lane), __builtin_amdgcn_readlane(v.y, lane)));
+}
+
+// The same panel by one wave, for m <= 64 positions: the pivot row passes through scalar registers, where the
+// workgroup's form needs a barrier and an LDS round trip per column.  Factor and solve of 64 rows in FP64: 74 us,
+// 91 with the workgroup's form throughout.  With two or four rows per lane the wave does the workgroup's
+// arithmetic by itself and loses what it saves (150 rows 245 and 275 us, 235 with this bound).
+template <class T>
+__device__ __forceinline__ void lu_panel_wave(T* A, int ld, int k0, int kb, int m, lds_ptr<int> perm, lds_ptr<T> pan,
+                                              bool keep, DenseSmem<T>& S) {
+  constexpr int PS = kBK + 1;
+  const int l = threadIdx.x & 63;
+  T p[kBK];        // columns t, t + 1, ... of the lane's row
+  int pos = l < m ? l : -1;
+  const int row = perm[k0 + min(l, m - 1)];
+  T* Ar = A + (size_t)row * ld + k0;
+#pragma unroll
+  for (int j = 0; j < kBK; ++j) p[j] = Ar[j];
+#pragma unroll 1
+  for (int t = 0; t < kb; ++t) {
+    const T a = fabs(p[0]);   // (a NaN is never taken)
+    const bool take = (pos >= t) & (a >= T(0));
+    const int wl = wave_argmax(take ? a : T(0), take ? pos : -1);
+    int pr = t;
+    T u[kBK];
+    if (wl < 0) {      // no comparable entry (all NaN): the column's own position, NaN throughout
+#pragma unroll
+      for (int j = 0; j < kBK; ++j) u[j] = T(NAN);
+    } else {
+      pr = __builtin_amdgcn_readlane(pos, wl);
+#pragma unroll
+      for (int j = 0; j < kBK; ++j) u[j] = lane_value(p[j], wl);
+    }
+    const T f = u[0] != T(0) ? p[0] / u[0] : T(0);
+    if (pos == pr) {
+      pos = t;
+#pragma unroll
+      for (int j = 0; j < kBK; ++j) S.u11[t * kBK + j] = u[j];
+    } else if (pos >= t) {
+      pos = pos == t ? pr : pos;
+      Ar[t] = f;
+      if (keep) pan[row * PS + t] = f;
+    }
+    // finished rows take the update too: their registers are not read again
+#pragma unroll
+    for (int j = 0; j + 1 < kBK; ++j) p[j] = p[j + 1] - f * u[j + 1];
+    p[kBK - 1] = T(0);
+  }
+  if (pos >= 0) perm[k0 + pos] = row;
+}
+
 // Up to 4 kBlock rows in FP64 and 6 kBlock in FP32: three rows per contact at the largest capacities that a
 // CU's LDS admits (330 contacts, and 814 cut at 1536 rows).  Returns perm (LDS, in lds).
 template <class T>
@@ -410,7 +467,9 @@ __device__ __forceinline__ lds_ptr<int> wg_lu_factor(T* A, int n, lds_ptr<T> lds
     const int kb = min(kBK, n - k0), m = n - k0, mm = ld - k0 - kBK;
     const bool u_lds = perm_len + PS * ld + kBK * mm <= lds_cap;
     __syncthreads();
-    if (m <= kBlock) lu_panel<T, 1>(A, ld, k0, kb, m, perm, pan, p_lds, S);
+    if (m <= 64) {
+      if (wave == 0) lu_panel_wave<T>(A, ld, k0, kb, m, perm, pan, p_lds, S);
+    } else if (m <= kBlock) lu_panel<T, 1>(A, ld, k0, kb, m, perm, pan, p_lds, S);
     else if (m <= 2 * kBlock) lu_panel<T, 2>(A, ld, k0, kb, m, perm, pan, p_lds, S);
     else if (m <= 4 * kBlock) lu_panel<T, 4>(A, ld, k0, kb, m, perm, pan, p_lds, S);
     else if constexpr (sizeof(T) == 4) lu_panel<T, 6>(A, ld, k0, kb, m, perm, pan, p_lds, S);
