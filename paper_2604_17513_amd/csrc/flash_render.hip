@@ -498,16 +498,20 @@ struct flash_renderer {
   EnvRef* d_envs = nullptr;
   float* d_boxes = nullptr;
   float4* d_tris = nullptr;
+  // a frame's cameras, obstacles and obstacle counts, one block on either side: one copy per frame
   DevCam* d_cams = nullptr;
   DevObs* d_obs = nullptr;
   int* d_nobs = nullptr;
-  std::vector<DevCam> h_cams;
-  std::vector<DevObs> h_obs;
-  std::vector<int> h_nobs;
+  void* h_frame = nullptr;            // pinned
+  size_t frame_bytes = 0;
+  DevCam* h_cams = nullptr;
+  DevObs* h_obs = nullptr;
+  int* h_nobs = nullptr;
 
   ~flash_renderer() {
     if (stream) (void)hipStreamSynchronize(stream);
     for (void* p : owned) (void)hipFree(p);
+    if (h_frame) (void)hipHostFree(h_frame);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
   }
   template <class X>
@@ -600,12 +604,19 @@ flash_status flash_renderer_create(const flash_env_desc* descs, int32_t n_envs, 
     HIPCHK(hipMemcpy(r->d_envs, r->envs.data(), n_envs * sizeof(EnvRef), hipMemcpyHostToDevice));
     r->d_boxes = r->alloc<float>((size_t)r->n_nodes * kNodeFloats);
     r->d_tris = r->alloc<float4>((size_t)r->n_leaves * kLeafVecs);
-    r->d_cams = r->alloc<DevCam>(n_envs);
-    r->d_obs = r->alloc<DevObs>((size_t)n_envs * FLASH_MAX_OBSTACLES);
-    r->d_nobs = r->alloc<int>(n_envs);
-    r->h_cams.resize(n_envs);
-    r->h_obs.resize((size_t)n_envs * FLASH_MAX_OBSTACLES);
-    r->h_nobs.resize(n_envs);
+    const size_t obs_at = n_envs * sizeof(DevCam);
+    const size_t nobs_at = obs_at + (size_t)n_envs * FLASH_MAX_OBSTACLES * sizeof(DevObs);
+    r->frame_bytes = nobs_at + n_envs * sizeof(int);
+    unsigned char* d = r->alloc<unsigned char>(r->frame_bytes);
+    HIPCHK(hipHostMalloc(&r->h_frame, r->frame_bytes, hipHostMallocDefault));
+    unsigned char* h = static_cast<unsigned char*>(r->h_frame);
+    std::memset(h, 0, r->frame_bytes);
+    r->d_cams = reinterpret_cast<DevCam*>(d);
+    r->d_obs = reinterpret_cast<DevObs*>(d + obs_at);
+    r->d_nobs = reinterpret_cast<int*>(d + nobs_at);
+    r->h_cams = reinterpret_cast<DevCam*>(h);
+    r->h_obs = reinterpret_cast<DevObs*>(h + obs_at);
+    r->h_nobs = reinterpret_cast<int*>(h + nobs_at);
   } catch (const FlashError& ex) {
     delete r;
     return flash::record_error(ex.st, ex.what());
@@ -649,10 +660,7 @@ flash_status flash_render(flash_renderer* r, const float* x_dev, int64_t ld, con
     }
   }
   try {
-    HIPCHK(hipMemcpyAsync(r->d_cams, r->h_cams.data(), ne * sizeof(DevCam), hipMemcpyHostToDevice, r->stream));
-    HIPCHK(hipMemcpyAsync(r->d_obs, r->h_obs.data(), r->h_obs.size() * sizeof(DevObs), hipMemcpyHostToDevice,
-                          r->stream));
-    HIPCHK(hipMemcpyAsync(r->d_nobs, r->h_nobs.data(), ne * sizeof(int), hipMemcpyHostToDevice, r->stream));
+    HIPCHK(hipMemcpyAsync(r->d_cams, r->h_frame, r->frame_bytes, hipMemcpyHostToDevice, r->stream));
     if (r->max_subtrees > 0)
       hipLaunchKernelGGL(k_refit, dim3((unsigned)r->max_subtrees, (unsigned)ne), dim3(kRefitBlock), 0, r->stream, x_dev,
                          (long long)ld, r->d_envs, r->d_cams, 0, r->d_boxes, r->d_tris);

@@ -227,13 +227,10 @@ def obstacle_struct(o: scenes.Obstacle) -> flash_obstacle:
     s = flash_obstacle()
     s.kind = o.kind
     s.move_steps = o.move_steps
-    for k in range(3):
-        s.center[k] = o.center[k]
-        s.size[k] = o.size[k]
-        s.lin_vel[k] = o.lin_vel[k]
-    R = np.asarray(o.rot, dtype=np.float64).reshape(3, 3)
-    for k in range(9):
-        s.rot[k] = R.reshape(-1)[k]
+    s.center[:] = o.center[0], o.center[1], o.center[2]
+    s.size[:] = o.size[0], o.size[1], o.size[2]
+    s.lin_vel[:] = o.lin_vel[0], o.lin_vel[1], o.lin_vel[2]
+    s.rot[:] = np.asarray(o.rot, dtype=np.float64).reshape(9).tolist()
     return s
 
 
@@ -582,14 +579,17 @@ def mlp_grad_noalloc(params_dev, x_dev, target_dev, n: int, grad_dev, loss_dev=N
 def camera_struct(cam) -> flash_camera:
     """cam: dict with position (3,), rot (3, 3) camera-to-world (columns: image right, image down,
     optical axis), fx, fy, cx, cy in pixels."""
-    s = flash_camera()
-    R = np.asarray(cam["rot"], dtype=np.float64).reshape(-1)
-    for k in range(3):
-        s.position[k] = float(cam["position"][k])
-    for k in range(9):
-        s.rot[k] = float(R[k])
-    s.fx, s.fy, s.cx, s.cy = float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"])
-    return s
+    return camera_array([cam])[0]
+
+
+def camera_array(cams):
+    """flash_camera array of the cameras (camera_struct), filled a row at a time."""
+    a = np.empty((len(cams), C.sizeof(flash_camera) // 8), dtype=np.float64)
+    for e, c in enumerate(cams):
+        a[e, :3] = c["position"][:3]
+        a[e, 3:12] = np.asarray(c["rot"], dtype=np.float64).reshape(-1)[:9]
+        a[e, 12:] = c["fx"], c["fy"], c["cx"], c["cy"]
+    return (flash_camera * len(cams)).from_buffer(a)
 
 
 class Renderer:
@@ -613,9 +613,7 @@ class Renderer:
         assert x_dev.dtype == torch.float32 and x_dev.is_cuda and x_dev.dim() == 2 and x_dev.shape[0] == 3
         x_dev = x_dev.contiguous()
         n = self.n_envs
-        cam_arr = (flash_camera * n)()
-        for e in range(n):
-            cam_arr[e] = camera_struct(cams[e])
+        cam_arr = camera_array([cams[e] for e in range(n)])
         ob_arr = (flash_obstacle * (n * MAX_OBSTACLES))()
         nob = (C.c_int32 * n)()
         if obstacles is not None:
