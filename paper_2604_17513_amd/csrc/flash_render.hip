@@ -30,6 +30,7 @@ using flash::FlashError;
 constexpr int kLeafTris = 4;
 constexpr int kMaxDepth = 48;         // create rejects deeper (binary) hierarchies
 constexpr int kGroupTris = 1024;      // triangles of a refit workgroup's subtree: 256 leaves, one per thread
+constexpr int kMaxEntries = 256;      // subtrees a workgroup chooses from, one per thread
 constexpr int kNone = INT32_MIN;      // no child, no node
 constexpr int kTile = 16;             // pixels per side of one workgroup's tile
 constexpr int kRefitBlock = 256;
@@ -37,6 +38,8 @@ constexpr float kEdgeBand = 1e-6f;    // barycentric band: FP32 solves of a ray 
 
 struct DevCam {
   float o[3], R[9], fx, fy, cx, cy;
+  float inv[9];   // of R
+  int cull;       // R is a rotation up to rounding: boxes may be projected onto the image
 };
 struct DevObs {
   float c[3], R[9], size[3];
@@ -59,11 +62,13 @@ struct Topo {
   std::vector<int32_t> leaf_tri;      // 3 per triangle, kLeafTris triangles per leaf, the last one repeated
   std::vector<Group> groups;          // the subtrees, then (if there are several) the nodes above them
   int n_subtrees = 0;
-  int levels = 0;                     // nodes on the longest path from the root
+  std::vector<int32_t> entries;       // at most kMaxEntries child slots (4 node + child) that cover the surface
+  int depth = 0, levels = 0;          // nodes on the longest path from the root, and below an entry
   // device
   int4* d_child = nullptr;
   int4* d_tri = nullptr;              // leaf_tri
   Group* d_groups = nullptr;
+  int* d_entries = nullptr;
 };
 
 // one env's part of a render
@@ -71,11 +76,13 @@ struct EnvRef {
   const int4* child;
   const int4* tri;
   const Group* groups;
+  const int* entries;
   long long node0;      // first of its nodes in the box array
   long long leaf0;      // first of its leaves in the triangle array
   int voff;             // first vertex column in x
   int n_nodes;
   int n_subtrees, n_groups;
+  int n_entries;
 };
 
 // The triangles a body shows: membrane triangles as given, or the faces of a tet mesh that
@@ -216,9 +223,27 @@ void build_bvh(Topo& T, const double* rest) {
     for (int i = 0; i < 4; ++i) k[i] = W[w].kids[i] >= 0 ? id[W[w].kids[i]] : W[w].kids[i];
     T.child[id[w]] = make_int4(k[0], k[1], k[2], k[3]);
   }
+  // entries: whole levels from the root down while they number at most kMaxEntries
   T.levels = 0;
   for (int g = 0; g < T.n_subtrees; ++g) T.levels = std::max(T.levels, T.groups[g].n_levels);
   if ((int)T.groups.size() > T.n_subtrees) T.levels += T.groups.back().n_levels;
+  T.depth = T.levels;
+  const int* code = reinterpret_cast<const int*>(T.child.data());
+  auto slots_of = [&](int node, std::vector<int32_t>& out) {
+    for (int c = 0; c < 4; ++c)
+      if (code[4 * node + c] != kNone) out.push_back(4 * node + c);
+  };
+  T.entries.clear();
+  slots_of((int)T.child.size() - 1, T.entries);
+  for (T.levels -= 1; T.levels > 0; --T.levels) {
+    std::vector<int32_t> below;
+    for (int s : T.entries) {
+      if (code[s] >= 0) slots_of(code[s], below);
+      else below.push_back(s);
+    }
+    if (below.size() > kMaxEntries) break;
+    T.entries = below;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -393,12 +418,42 @@ __device__ float obstacle_hit(const DevObs& ob, float3 o, float3 d) {
   return best;
 }
 
+// Whether some ray of the pixels [u0, u0 + kTile) x [v0, v0 + kTile) may enter a box given relative to the camera
+// (conservative: only boxes whose projection, with its rounding, lies outside are dropped); *key: its least depth.
+__device__ bool tile_may_see(const DevCam& cam, const float (&lo)[3], const float (&hi)[3], int u0, int v0, float* key) {
+  float zmin = INFINITY, pmax = 0.0f, ulo = INFINITY, uhi = -INFINITY, vlo = INFINITY, vhi = -INFINITY;
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const float x = c & 1 ? hi[0] : lo[0], y = c & 2 ? hi[1] : lo[1], z = c & 4 ? hi[2] : lo[2];
+    const float* I = cam.inv;
+    const float X = I[0] * x + I[1] * y + I[2] * z, Y = I[3] * x + I[4] * y + I[5] * z,
+                Z = I[6] * x + I[7] * y + I[8] * z;
+    const float rz = __builtin_amdgcn_rcpf(Z);   // (one unit in the last place, inside the pad)
+    const float u = cam.fx * (X * rz), v = cam.fy * (Y * rz);
+    bad = bad || !(fabsf(u) < INFINITY) || !(fabsf(v) < INFINITY) || !(Z > 0.0f);
+    zmin = fminf(zmin, Z);
+    pmax = fmaxf(pmax, fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))));
+    ulo = fminf(ulo, u); uhi = fmaxf(uhi, u);
+    vlo = fminf(vlo, v); vhi = fmaxf(vhi, v);
+  }
+  *key = zmin;
+  if (bad || !(zmin > 1e-3f * pmax)) return true;   // near or behind the camera's plane
+  const float k = pmax / zmin;
+  const float pad = 1.0f + 4e-6f * (fmaxf(cam.fx, cam.fy) * k * (1.0f + k) + fabsf(cam.cx) + fabsf(cam.cy));
+  const float ul = (float)u0 + 0.5f - cam.cx, vl = (float)v0 + 0.5f - cam.cy;
+  return !(uhi + pad < ul) && !(ulo - pad > ul + kTile) && !(vhi + pad < vl) && !(vlo - pad > vl + kTile);
+}
+
 // One workgroup renders one 16 x 16 tile of one env's image, 8 x 8 pixels per wave; stack: LDS ints, one
-// column per thread.  What bounds it: vector instructions of the slab and triangle tests.  Four children per
-// node halve the dependent loads of a descent; their boxes and a leaf's triangles are read 16 bytes at a
+// column per thread.  What bounds it: vector instructions of the slab and triangle tests.  PICK: the workgroup
+// first picks, with one test per thread, the subtrees (of up to kMaxEntries) whose boxes project onto the tile,
+// nearest first; each ray starts at those, which spares it the upper half of the descent.  Four children per
+// node halve the dependent loads of the rest; their boxes and a leaf's triangles are read 16 bytes at a
 // time; lanes go on through inner nodes until the wave's all have a leaf, so that the triangle tests run
 // together.  One 128 x 128 image of a 64800-triangle sheet: 32 us (81 us with binary nodes, triangles through
-// their vertex ids and the stack in scratch); 48 of 640 x 480: 711 us (1445 us).
+// their vertex ids and the stack in scratch); 48 of 640 x 480: 590 us, 711 from the root, 1445 us before.
+template <bool PICK>
 __global__ void __launch_bounds__(kTile * kTile) k_render(const float4* __restrict__ tris,
                                                           const EnvRef* __restrict__ envs,
                                                           const float* __restrict__ boxes, const DevCam* __restrict__ cams,
@@ -406,14 +461,53 @@ __global__ void __launch_bounds__(kTile * kTile) k_render(const float4* __restri
                                                           int width, int height, int tiles_x, float* depth,
                                                           int* inst, float* pts) {
   extern __shared__ int stack_lds[];
+  constexpr int NE = PICK ? kMaxEntries : 1;
+  __shared__ float s_box[6][NE], s_key[NE];
+  __shared__ int s_code[NE], s_order[NE];
+  __shared__ int s_count[kTile * kTile / 64];
   const int e = blockIdx.y;
   const int tile = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int u = (tile % tiles_x) * kTile + 8 * (wave & 1) + (lane & 7);
-  const int v = (tile / tiles_x) * kTile + 8 * (wave >> 1) + (lane >> 3);
-  if (u >= width || v >= height) return;
+  const int u0 = (tile % tiles_x) * kTile, v0 = (tile / tiles_x) * kTile;
   const EnvRef E = envs[e];
-  const DevCam cam = cams[e];
+  const DevCam& cam = cams[e];
+  int n_entries = 0;
+  if constexpr (PICK) {
+    float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0}, key = 0.0f;
+    int code = kNone;
+    bool keep = false;
+    if ((int)threadIdx.x < E.n_entries) {
+      const int s = E.entries[threadIdx.x];
+      const float* b = boxes + kNodeFloats * (E.node0 + (s >> 2)) + (s & 3);
+      for (int k = 0; k < 3; ++k) { lo[k] = b[4 * k]; hi[k] = b[12 + 4 * k]; }
+      code = reinterpret_cast<const int*>(E.child)[s];
+      keep = tile_may_see(cam, lo, hi, u0, v0, &key) | !cam.cull;
+    }
+    const unsigned long long m = __ballot(keep);
+    if (lane == 0) s_count[wave] = __popcll(m);
+    __syncthreads();
+    int at = __popcll(m & ((1ull << lane) - 1ull));
+    for (int w = 0; w < kTile * kTile / 64; ++w) {
+      if (w < wave) at += s_count[w];
+      n_entries += s_count[w];
+    }
+    if (keep) {
+      for (int k = 0; k < 3; ++k) { s_box[k][at] = lo[k]; s_box[3 + k][at] = hi[k]; }
+      s_code[at] = code;
+      s_key[at] = key == key ? key : -INFINITY;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < n_entries) {   // nearest first, ties in list order
+      const float mine = s_key[threadIdx.x];
+      int rank = 0;
+      for (int q = 0; q < n_entries; ++q) rank += (s_key[q] < mine) | ((s_key[q] == mine) & (q < (int)threadIdx.x));
+      s_order[rank] = threadIdx.x;
+    }
+    __syncthreads();
+  }
+  const int u = u0 + 8 * (wave & 1) + (lane & 7);
+  const int v = v0 + 8 * (wave >> 1) + (lane >> 3);
+  if (u >= width || v >= height) return;
   const float xn = ((float)u + 0.5f - cam.cx) / cam.fx;
   const float yn = ((float)v + 0.5f - cam.cy) / cam.fy;
   const float3 o = make_float3(cam.o[0], cam.o[1], cam.o[2]);
@@ -423,13 +517,27 @@ __global__ void __launch_bounds__(kTile * kTile) k_render(const float4* __restri
   const float3 inv = make_float3(1.0f / d.x, 1.0f / d.y, 1.0f / d.z);
   float tbest = INFINITY;
   int ibest = -1;
-  if (E.n_nodes > 0) {
+  if (PICK ? n_entries > 0 : E.n_nodes > 0) {
     const float4* bx = reinterpret_cast<const float4*>(boxes + kNodeFloats * E.node0);
     const float4* tr = tris + kLeafVecs * E.leaf0;
     int* stack = stack_lds + threadIdx.x;
-    int sp = 0;
-    int cur = E.n_nodes - 1;
+    int sp = 0, next = 0;
+    if (!PICK) stack[kTile * kTile * sp++] = E.n_nodes - 1;
     for (;;) {
+      int cur = kNone;
+      if (sp > 0) {
+        cur = stack[kTile * kTile * --sp];
+      } else {
+        while (next < n_entries) {
+          const int q = s_order[next++];
+          if (slab_entry(s_box[0][q], s_box[1][q], s_box[2][q], s_box[3][q], s_box[4][q], s_box[5][q], inv, tbest) <
+              INFINITY) {
+            cur = s_code[q];
+            break;
+          }
+        }
+        if (cur == kNone) break;
+      }
       while (cur >= 0) {
         const float4* b = bx + kNodeFloats / 4 * (size_t)cur;
         const float4 lx = b[0], ly = b[1], lz = b[2], hx = b[3], hy = b[4], hz = b[5];
@@ -452,7 +560,7 @@ __global__ void __launch_bounds__(kTile * kTile) k_render(const float4* __restri
         cur = near_c ? nc : na;
         if (!(fminf(ta, tc) < INFINITY)) cur = sp > 0 ? stack[kTile * kTile * --sp] : kNone;
       }
-      if (cur == kNone) break;
+      if (cur == kNone) continue;
       float4 q[kLeafVecs];
 #pragma unroll
       for (int k = 0; k < kLeafVecs; ++k) q[k] = tr[kLeafVecs * (size_t)(-1 - cur) + k];
@@ -463,7 +571,6 @@ __global__ void __launch_bounds__(kTile * kTile) k_render(const float4* __restri
                                  make_float3(b.z, b.w, q[3 * t + 2].x));
         if (th < tbest) { tbest = th; ibest = 0; }
       }
-      cur = sp > 0 ? stack[kTile * kTile * --sp] : kNone;
     }
   }
   const int no = nobs[e];
@@ -492,7 +599,7 @@ struct flash_renderer {
   std::vector<EnvRef> envs;
   std::vector<int> voff;
   long long n_nodes = 0, n_leaves = 0;
-  int max_subtrees = 0, max_levels = 0;
+  int max_subtrees = 0, max_levels = 0, max_depth = 0;
   bool any_top = false;               // some env has nodes above its subtrees
   std::vector<void*> owned;
   EnvRef* d_envs = nullptr;
@@ -522,6 +629,25 @@ struct flash_renderer {
     return static_cast<X*>(p);
   }
 };
+
+// Inverse of a camera's R; false where R is no rotation (to 1e-3) and boxes cannot be projected with it.
+static bool rotation_inverse(const double* R, float* inv) {
+  bool ok = true;
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) {
+      double g = 0.0;
+      for (int k = 0; k < 3; ++k) g += R[3 * k + i] * R[3 * k + j];
+      ok = ok && std::fabs(g - (i == j ? 1.0 : 0.0)) < 1e-3;
+    }
+  const double det = R[0] * (R[4] * R[8] - R[5] * R[7]) - R[1] * (R[3] * R[8] - R[5] * R[6]) +
+                     R[2] * (R[3] * R[7] - R[4] * R[6]);
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) {
+      const int a = (j + 1) % 3, b = (j + 2) % 3, c = (i + 1) % 3, d = (i + 2) % 3;
+      inv[3 * i + j] = ok ? (float)((R[3 * a + c] * R[3 * b + d] - R[3 * a + d] * R[3 * b + c]) / det) : 0.0f;
+    }
+  return ok;
+}
 
 extern "C" {
 
@@ -575,13 +701,16 @@ flash_status flash_renderer_create(const flash_env_desc* descs, int32_t n_envs, 
       T.d_child = r->alloc<int4>(T.child.size());
       T.d_tri = r->alloc<int4>(T.leaf_tri.size() / 4);
       T.d_groups = r->alloc<Group>(T.groups.size());
+      T.d_entries = r->alloc<int>(T.entries.size());
       if (!T.child.empty()) {
         HIPCHK(hipMemcpy(T.d_child, T.child.data(), T.child.size() * sizeof(int4), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(T.d_tri, T.leaf_tri.data(), T.leaf_tri.size() * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(T.d_groups, T.groups.data(), T.groups.size() * sizeof(Group), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(T.d_entries, T.entries.data(), T.entries.size() * sizeof(int), hipMemcpyHostToDevice));
       }
       r->max_subtrees = std::max(r->max_subtrees, T.n_subtrees);
       r->max_levels = std::max(r->max_levels, T.levels);
+      r->max_depth = std::max(r->max_depth, T.depth);
       r->any_top |= (int)T.groups.size() > T.n_subtrees;
     }
     for (int e = 0; e < n_envs; ++e) {
@@ -596,6 +725,8 @@ flash_status flash_renderer_create(const flash_env_desc* descs, int32_t n_envs, 
       E.n_nodes = (int)T.child.size();
       E.n_subtrees = T.n_subtrees;
       E.n_groups = (int)T.groups.size();
+      E.entries = T.d_entries;
+      E.n_entries = (int)T.entries.size();
       r->n_nodes += E.n_nodes;
       r->n_leaves += (long long)T.leaf_tri.size() / (3 * kLeafTris);
       r->envs.push_back(E);
@@ -647,6 +778,7 @@ flash_status flash_render(flash_renderer* r, const float* x_dev, int64_t ld, con
     DevCam& c = r->h_cams[e];
     for (int k = 0; k < 3; ++k) c.o[k] = (float)cams[e].position[k];
     for (int k = 0; k < 9; ++k) c.R[k] = (float)cams[e].rot[k];
+    c.cull = rotation_inverse(cams[e].rot, c.inv) ? 1 : 0;
     c.fx = (float)cams[e].fx; c.fy = (float)cams[e].fy; c.cx = (float)cams[e].cx; c.cy = (float)cams[e].cy;
     r->h_nobs[e] = no;
     for (int q = 0; q < no; ++q) {
@@ -668,9 +800,15 @@ flash_status flash_render(flash_renderer* r, const float* x_dev, int64_t ld, con
       hipLaunchKernelGGL(k_refit, dim3(1, (unsigned)ne), dim3(kRefitBlock), 0, r->stream, x_dev, (long long)ld,
                          r->d_envs, r->d_cams, 1, r->d_boxes, r->d_tris);
     const int tx = (width + kTile - 1) / kTile, ty = (height + kTile - 1) / kTile;
+    // Subtrees are picked per tile where an image has at least as many tiles as a surface has entries, so that a
+    // tile sees few of them: 48 frames of 640 x 480 784 us with, 919 without (whole calls, a 64800-triangle sheet),
+    // of 320 x 240 418 and 446; below, testing a tile's many entries costs what it saves (16 frames of 128 x 128
+    // 164 with, 148 without, one frame 85 and 69).
+    const bool pick = tx * ty >= kMaxEntries;
     // a node leaves at most three children on the stack on the way down
-    const size_t lds = (size_t)kTile * kTile * sizeof(int) * (3 * r->max_levels + 1);
-    hipLaunchKernelGGL(k_render, dim3((unsigned)(tx * ty), (unsigned)ne), dim3(kTile * kTile), lds, r->stream,
+    const size_t lds = (size_t)kTile * kTile * sizeof(int) * (3 * (pick ? r->max_levels : r->max_depth) + 1);
+    const auto kernel = pick ? k_render<true> : k_render<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tx * ty), (unsigned)ne), dim3(kTile * kTile), lds, r->stream,
                        (const float4*)r->d_tris, r->d_envs, (const float*)r->d_boxes, r->d_cams, r->d_obs, r->d_nobs,
                        width, height, tx, depth_dev, instance_dev, points_dev);
     HIPCHK(hipGetLastError());
