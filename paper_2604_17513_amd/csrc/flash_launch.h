@@ -104,8 +104,8 @@ __host__ __device__ constexpr size_t csp_smem_bytes(int cap, int rlds) {
 }
 // LDS of one gfx950 CU: the most one workgroup can be given, static and dynamic together.
 constexpr size_t kLdsBytes = 160 * 1024;
-// Reserve for the static LDS of the contact-solve kernels (k_csp and the fused loop: 4160 bytes
-// with the FP64 contact solve, 2112 with the FP32 one); create checks the kernels' real static
+// Reserve for the static LDS of the contact-solve kernels (k_csp and the fused loop: 5408 bytes
+// with the FP64 contact solve, 2752 with the FP32 one); create checks the kernels' real static
 // LDS against it.
 constexpr size_t kCspStaticLds = 8192;
 // Raises the dynamic LDS limit of the contact-solve kernels (both contact-solve precisions, per

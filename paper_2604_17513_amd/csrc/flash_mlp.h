@@ -25,15 +25,30 @@ struct MlpLayout {
 };
 static_assert(MlpLayout::total == 35587, "parameter count");
 
-// Gradient slabs: a workgroup of the gradient kernel takes kGradRows rows at a time and sums into a slab of
-// its own.  At most one workgroup per CU (its LDS), so at most kMaxSlabs slabs.
+// Gradient slabs: a workgroup of the gradient kernel takes grad_span(rows) rows at a time and sums into a slab of
+// its own.  At most one workgroup per CU (its LDS), so at most kMaxSlabs slabs; up to 256 rows go into one sum,
+// and more are split evenly.
 constexpr long kGradRows = 128;
 constexpr long kMaxSlabs = 256;
 constexpr long kSlab = (MlpLayout::total + 3) / 4 * 4;
-inline long grad_slabs(long rows) {
+inline int grad_span(long rows) {
   const long b = (rows + kGradRows - 1) / kGradRows;
+  if (b <= 2 || b > kMaxSlabs) return (int)kGradRows;
+  return (int)(((rows + b - 1) / b + 7) / 8 * 8);
+}
+inline long grad_slabs(long rows) {
+  if (rows <= 2 * kGradRows) return 1;
+  const long span = grad_span(rows), b = (rows + span - 1) / span;
   return b < kMaxSlabs ? b : kMaxSlabs;
 }
+// Scratch of one gradient of up to `rows` rows: grad_slabs slabs and doubles, and dz of three layers and of the
+// output per row.
+struct GradScratch {
+  float* slab;
+  double* partial;
+  float* dz;        // [3][kHidden / 4][rows][4], 16-byte aligned
+  float* dy;        // [rows][kOut]
+};
 
 // Device buffers of an inference pass over the contact slots of a batch.
 struct MlpBuffers {
@@ -51,14 +66,13 @@ void prepare_mlp();
 // features; need != nullptr: 32-row tiles without a flagged row are skipped.
 void launch_mlp_fused(const float* W, const float* norm, const float* X, long rows, const int* need, float* Y,
                       hipStream_t s);
-// Mean squared loss of rows (X, Lab) and its gradient; slab: grad_slabs(rows) * kSlab floats, partial:
-// grad_slabs(rows) doubles.
-void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss, float* slab,
-                     double* partial, hipStream_t s);
+// Mean squared loss of rows (X, Lab) and its gradient.
+void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss,
+                     const GradScratch& g, hipStream_t s);
 // One minibatch of training: rows idx of the raw features and labels, normalised with norm; Adam step t on
 // W, m, v; the loss before the step.
 void launch_mlp_train(float* W, const float* norm, const float* feat, const float* lab, const int* idx, long rows,
-                      float* m, float* v, float lr, int t, float* loss, float* slab, double* partial, hipStream_t s);
+                      float* m, float* v, float lr, int t, float* loss, const GradScratch& g, hipStream_t s);
 void mlp_loss(const float* Y, const float* Lab, long n, double* partial, float* loss, hipStream_t s);
 void launch_gather_batch(const float* feat, const float* lab, const int* idx, int B, const float* norm, float* X,
                          float* Y, hipStream_t s);

@@ -258,11 +258,14 @@ void launch_mlp_fused(const float* W, const float* norm, const float* X, long ro
 }
 
 // ---------------------------------------------------------------------------
-// Loss and gradient of a minibatch in two launches: k_mlp_grad takes 128 rows per workgroup (32 per wave)
+// Loss and gradient of a minibatch in two launches: k_mlp_grad takes up to 128 rows per workgroup (32 per wave)
 // through the forward pass, the loss and the whole backward pass, and leaves the block's share of every
-// parameter gradient in the workgroup's slab; k_mlp_reduce adds the slabs in order and, in training, applies
-// Adam.  A wave's activations stay in its registers as bf16 operands; the weight gradients, which contract
-// over rows, take their operands from LDS copies [neuron][row] of one layer at a time.
+// weight gradient in the workgroup's slab and the rows' dz in memory; k_mlp_reduce adds the slabs in order, sums
+// dz over the rows for the biases and, in training, applies Adam.  A wave's activations stay in its registers as
+// bf16 operands; the weight gradients, which contract over rows, take their operands from LDS copies
+// [neuron][row] of one layer at a time.  The backward products add their terms in natural order, 16 at a time
+// (the bits of two products of 8), and rows are split as the weight gradients' sums always were, so training keeps
+// its bits.
 // ---------------------------------------------------------------------------
 struct GradSmem {
   __bf16 w1[kHidden * kLd1];
@@ -273,7 +276,6 @@ struct GradSmem {
   float nrm[kNorm + 1];
   __bf16 dz[kHidden * kLdH];    // loss gradient of a layer's pre-activations [neuron][row]
   __bf16 hin[kHidden * kLdH];   // that layer's inputs [neuron][row]
-  float bias[4 * kHidden];      // per-wave sums of dz over rows
   double e2[kWaves];
 };
 constexpr size_t kGradSmem = sizeof(GradSmem);
@@ -317,7 +319,7 @@ __device__ __forceinline__ void put_blocks(const float (&f)[kBlocks][8], __bf16*
     }
 }
 
-// From those rows to registers, and back as rows of the transpose (the outputs, its columns, permuted).
+// From those rows to registers, and back as rows of the transpose.
 __device__ __forceinline__ void read_blocks(const __bf16* src, bf16x4 (&w)[kBlocks][2]) {
 #pragma unroll
   for (int u = 0; u < kBlocks; ++u)
@@ -331,7 +333,7 @@ __device__ __forceinline__ void put_transposed(const bf16x4 (&w)[kBlocks][2], __
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const bf16x2 c = {w[u][0][t], w[u][1][t]};
-      *reinterpret_cast<bf16x2*>(dst + (block_col(u) + t) * kLdH + perm16(block_row(u))) = c;
+      *reinterpret_cast<bf16x2*>(dst + (block_col(u) + t) * kLdH + block_row(u)) = c;
     }
 }
 
@@ -346,40 +348,44 @@ __device__ __forceinline__ void put_rows(__bf16* dst, const bf16x8 (&op)[4][2], 
         dst[(32 * mt + 16 * p + 8 * (t >> 2) + 4 * h + (t & 3)) * kLdH + col] = valid ? op[mt][p][t] : (__bf16)0.f;
 }
 
-// One exchange of bias_sums: of 2 N values each lane keeps N, added to its partner's.
-template <int N, int S>
-__device__ __forceinline__ void halve(float (&v)[16], int l) {
-  const bool up = (l & S) != 0;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const float keep = up ? v[i + N] : v[i], give = up ? v[i] : v[i + N];
-    v[i] = keep + __shfl_xor(give, S);
-  }
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+
+// acc + A B for 8 terms, lane l holding the terms 4 (l / 32) + t of its row of A and its column of B.
+__device__ __forceinline__ floatx16 mfma8(bf16x4 a, bf16x4 b, floatx16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4, a), __builtin_bit_cast(shortx4, b), acc, 0,
+                                                  0, 0);
 }
 
-// Sums of a tile's 16 neurons over the wave's rows, halving the values a lane holds at each exchange.
-__device__ __forceinline__ void bias_sums(float (&v)[16], float* dst, int mt, int l) {
-  halve<8, 16>(v, l);
-  halve<4, 8>(v, l);
-  halve<2, 4>(v, l);
-  halve<1, 2>(v, l);
-  v[0] += __shfl_xor(v[0], 1);
-  const int r = (l & 31) >> 1;
-  if ((l & 1) == 0) dst[32 * mt + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)] = v[0];
-}
-
-// ReLU mask, bias sums and rounding of one tile of dz.
-__device__ __forceinline__ void dz_tile(const floatx16& acc, unsigned mask, int mt, int l, float* bias, bf16x8 (&out)[2]) {
+// ReLU mask, store (at d, when there is a row, in the layout [column / 4][rows][4]) and rounding of one tile of dz.
+__device__ __forceinline__ void dz_tile(const floatx16& acc, unsigned mask, int mt, int h, float* d, long rows,
+                                        bf16x8 (&out)[2]) {
   float v[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = (mask >> r) & 1u ? acc[r] : 0.f;
+  if (d) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(d + (8 * mt + 2 * q + h) * rows * 4) =
+          make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+  }
   round_tile(v, out);
-  bias_sums(v, bias, mt, l);
 }
 
 // dz of the layer below from this layer's (operands din) through the transposed weights wt.
 __device__ __forceinline__ void dz_below(const __bf16* wt, const bf16x8 (&din)[4][2], const unsigned (&mask)[4], int l,
-                                         float* bias, bf16x8 (&dout)[4][2]) {
+                                         float* d, long rows, bf16x8 (&dout)[4][2]) {
+  // The operands with k = 8 (l / 32) + t natural, from 4 (l / 32) + t of either 8: the upper lanes' first halves
+  // change places with the lower lanes' second.  Products of 16 in natural order have the bits of two of 8.
+  bf16x8 nat[4][2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const uint4 u = __builtin_bit_cast(uint4, din[q][p]);
+      const auto a = __builtin_amdgcn_permlane32_swap(u.x, u.z, false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(u.y, u.w, false, false);
+      nat[q][p] = __builtin_bit_cast(bf16x8, make_uint4(a[0], b[0], a[1], b[1]));
+    }
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
     const __bf16* wrow = wt + (32 * mt + (l & 31)) * kLdH + 8 * (l >> 5);
@@ -389,34 +395,34 @@ __device__ __forceinline__ void dz_below(const __bf16* wt, const bf16x8 (&din)[4
 #pragma unroll
       for (int p = 0; p < 2; ++p)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(wrow + 32 * q + 16 * p),
-                                                      din[q][p], acc, 0, 0, 0);
-    dz_tile(acc, mask[mt], mt, l, bias, dout[mt]);
+                                                      nat[q][p], acc, 0, 0, 0);
+    dz_tile(acc, mask[mt], mt, l >> 5, d, rows, dout[mt]);
     __builtin_amdgcn_sched_barrier(0);   // one tile's operands in flight, not all four's
   }
 }
 
-// One 32 x 32 tile of dz hin^T over the block's rows; mrow, nrow: this lane's rows of the two operands.
-__device__ __forceinline__ floatx16 row_product(const __bf16* mrow, const __bf16* nrow) {
-  floatx16 acc = {};
+// acc plus one 32 x 32 tile of dz hin^T over the block's rows; mrow, nrow: this lane's rows of the two operands.
+__device__ __forceinline__ floatx16 row_product(const __bf16* mrow, const __bf16* nrow, floatx16 acc) {
 #pragma unroll
   for (int k = 0; k < kGradRows; k += 16)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(mrow + k),
-                                                  *reinterpret_cast<const bf16x8*>(nrow + k), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(mrow + k), *reinterpret_cast<const bf16x8*>(nrow + k), acc, 0, 0, 0);
   return acc;
 }
 
-__device__ __forceinline__ void put(float* p, float v, bool first) { *p = first ? v : *p + v; }
-
-// A lane's 16 values of a 32 x 32 tile to column c of G (row stride ld).
-__device__ __forceinline__ void put_tile(float* G, int ld, int row0, int c, int h, const floatx16& v, bool first) {
+// A lane's 16 values of a 32 x 32 tile of G (row stride ld), column c: zeros for a slab's first block of rows,
+// else what the earlier blocks left; and back.
+__device__ __forceinline__ floatx16 get_tile(const float* G, int ld, int row0, int c, int h, bool first) {
+  const float* p = G + (row0 + 4 * h) * ld + c;
+  floatx16 v = {};
+  if (!first)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = p[(8 * (r >> 2) + (r & 3)) * ld];
+  return v;
+}
+__device__ __forceinline__ void put_tile(float* G, int ld, int row0, int c, int h, const floatx16& v) {
   float* p = G + (row0 + 4 * h) * ld + c;
-  if (first) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * ld] = v[r];
-  } else {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * ld] += v[r];
-  }
+  for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * ld] = v[r];
 }
 
 // The 128 x 128 weight gradient of a hidden layer: wave w takes the 32 inputs 32 w .. and all outputs.
@@ -424,35 +430,29 @@ __device__ __forceinline__ void hidden_wgrad(const GradSmem& S, float* G, int l,
   const int h = l >> 5, c = 32 * wave + (l & 31);
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
-    const floatx16 acc = row_product(S.dz + (32 * mt + (l & 31)) * kLdH + 8 * h, S.hin + c * kLdH + 8 * h);
-    put_tile(G, kHidden, 32 * mt, c, h, acc, first);
+    put_tile(G, kHidden, 32 * mt, c, h,
+             row_product(S.dz + (32 * mt + (l & 31)) * kLdH + 8 * h, S.hin + c * kLdH + 8 * h,
+                         get_tile(G, kHidden, 32 * mt, c, h, first)));
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-__device__ __forceinline__ void put_bias(const GradSmem& S, float* G, bool first) {
-  const int t = threadIdx.x;
-  if (t < kHidden)
-    put(G + t, (S.bias[t] + S.bias[kHidden + t]) + (S.bias[2 * kHidden + t] + S.bias[3 * kHidden + t]), first);
-}
-
 // Rows idx[r] (or r) of feat and lab, normalised with norm (or as they are).  Workgroup b takes the blocks of
-// kGradRows rows b, b + gridDim.x, ...; its sums go to slab[b][MlpLayout] and partial[b] (squared errors).
+// `span` rows (at most kGradRows) b, b + gridDim.x, ...; its sums go to slab[b][MlpLayout] and partial[b] (squared
+// errors), the rows' dz to dz[layer 1..3][kHidden / 4][rows][4] and dy[rows][kOut].
 // What bounds it: latency of one wave per SIMD through ten dependent products, then LDS traffic of the
-// [neuron][row] copies; activations and their gradients never reach memory.  A minibatch of 4096 (32
-// workgroups): 25 us and 5 us for the reduction; separate kernels per product, mask, sum and layer (21 launches,
-// activations through memory) took 300 us.  Of the 25: weights 2, forward pass 4, transposing 1.5, the three
-// dz layers 2.2 each, the weight gradients 1.5 each, row copies 0.6 each.
+// [neuron][row] copies; activations never reach memory.  A minibatch of 4096 (32
+// workgroups): 28 us and 7 us for the reduction; separate kernels per product, mask, sum and layer (21 launches,
+// activations through memory) took 300 us.
 __global__ void __launch_bounds__(64 * kWaves, 1) k_mlp_grad(const float* W, const float* norm, const float* feat,
-                                                             const float* lab, const int* idx, long rows, float* slab,
-                                                             double* partial) {
+                                                             const float* lab, const int* idx, long rows, int span,
+                                                             float* slab, double* partial, float* dz, float* dy_out) {
   extern __shared__ __align__(16) unsigned char gsm_raw[];
   GradSmem& S = *reinterpret_cast<GradSmem*>(gsm_raw);
   const MlpLayout L;
   const int wave = threadIdx.x >> 6;
-  const long nblk = (rows + kGradRows - 1) / kGradRows;
+  const long nblk = (rows + span - 1) / span;
   float* G = slab + (size_t)blockIdx.x * kSlab;
-  float* wbias = S.bias + wave * kHidden;
   for (long blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
     const bool first = blk == blockIdx.x;
     int l = threadIdx.x & 63;
@@ -467,9 +467,11 @@ __global__ void __launch_bounds__(64 * kWaves, 1) k_mlp_grad(const float* W, con
       put_blocks(f2, S.w2);
       put_blocks(f3, S.w3);
     }
-    const long row = blk * kGradRows + col;
-    const bool valid = row < rows;
+    const long row = blk * span + col;
+    const bool valid = row < rows && col < span;
     const long at = valid ? row : rows - 1;
+    float* drow = valid ? dz + row * 4 : nullptr;
+    const long layer = rows * kHidden;
     const long src = idx ? idx[at] : at;
     float target[kOut];
     for (int k = 0; k < kOut; ++k) target[k] = lab[src * kOut + k];
@@ -494,96 +496,123 @@ __global__ void __launch_bounds__(64 * kWaves, 1) k_mlp_grad(const float* W, con
     for (int s = 32; s > 0; s >>= 1) e2 += __shfl_xor(e2, s);
     if (l == 0) S.e2[wave] = e2;
     // output layer: its inputs and dy to LDS; dz3 (= W4^T dy) needs no transposed copy
-    bf16x8 dyb;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) dyb[t] = (__bf16)0.f;
     const bf16x2 d01 = to_bf2(dy[0], dy[1]), d2 = to_bf2(dy[2], 0.f);
-    dyb[0] = d01[0];
-    dyb[1] = d01[1];
-    dyb[2] = d2[0];
+    const bf16x4 dyb = {d01[0], d01[1], d2[0], (__bf16)0.f};
     if (h == 0)
 #pragma unroll
       for (int k = 0; k < kOut; ++k) S.dz[k * kLdH + col] = dyb[k];
     put_rows(S.hin, h3[0], col, h, valid);
-    float db4[kOut];
+    if (valid && h == 0)
 #pragma unroll
-    for (int k = 0; k < kOut; ++k) {
-      db4[k] = dy[k];
-      for (int s = 16; s > 0; s >>= 1) db4[k] += __shfl_xor(db4[k], s);
-      if (l == 0) wbias[k] = db4[k];
-    }
+      for (int k = 0; k < kOut; ++k) dy_out[row * kOut + k] = dy[k];
     __syncthreads();   // forward weights free, dy and h3 written
     {
-      const floatx16 acc = row_product(S.dz + min(l & 31, kOut - 1) * kLdH + 8 * h, S.hin + col * kLdH + 8 * h);
+      floatx16 acc = {};
+      if (!first && h == 0)
+#pragma unroll
+        for (int k = 0; k < kOut; ++k) acc[k] = G[L.w4 + k * kHidden + col];
+      acc = row_product(S.dz + min(l & 31, kOut - 1) * kLdH + 8 * h, S.hin + col * kLdH + 8 * h, acc);
       if (h == 0)
 #pragma unroll
-        for (int k = 0; k < kOut; ++k) put(G + L.w4 + k * kHidden + col, acc[k], first);
-      const int t = threadIdx.x;
-      if (t < kOut)
-        put(G + L.b4 + t, (S.bias[t] + S.bias[kHidden + t]) + (S.bias[2 * kHidden + t] + S.bias[3 * kHidden + t]), first);
-      if (t == 0) partial[blockIdx.x] = (first ? 0.0 : partial[blockIdx.x]) + ((S.e2[0] + S.e2[1]) + (S.e2[2] + S.e2[3]));
+        for (int k = 0; k < kOut; ++k) G[L.w4 + k * kHidden + col] = acc[k];
+      if (threadIdx.x == 0) partial[blockIdx.x] = (first ? 0.0 : partial[blockIdx.x]) + ((S.e2[0] + S.e2[1]) + (S.e2[2] + S.e2[3]));
     }
     bf16x4 w2[kBlocks][2], w3[kBlocks][2];
     read_blocks(S.w3, w3);
     read_blocks(S.w2, w2);
-    bf16x8 w4t[4];
+    bf16x4 w4t[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
-        w4t[mt][t] = t < kOut ? (h == 0 ? S.w4[t * kLdH + perm16(32 * mt + (l & 31))] : (__bf16)0.f) : (__bf16)0.f;
-    __syncthreads();   // dy, h3, the weights' rows and the bias sums read
+      for (int t = 0; t < 4; ++t)
+        w4t[mt][t] = t < kOut && h == 0 ? S.w4[t * kLdH + perm16(32 * mt + (l & 31))] : (__bf16)0.f;
+    __syncthreads();   // dy, h3 and the weights' rows read
     put_transposed(w3, S.w3);
     put_transposed(w2, S.w2);
     bf16x8 dz3[4][2], dz2[4][2], dz1[4][2];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       floatx16 acc = {};
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w4t[mt], dyb, acc, 0, 0, 0);
-      dz_tile(acc, m3[0][mt], mt, l, wbias, dz3[mt]);
+      acc = mfma8(w4t[mt], dyb, acc);
+      dz_tile(acc, m3[0][mt], mt, h, drow ? drow + 2 * layer : nullptr, rows, dz3[mt]);
       __builtin_amdgcn_sched_barrier(0);
     }
     put_rows(S.dz, dz3, col, h, true);
     put_rows(S.hin, h2[0], col, h, valid);
     __syncthreads();
-    put_bias(S, G + L.b3, first);
     hidden_wgrad(S, G + L.w3, l, wave, first);
     __syncthreads();
-    dz_below(S.w3, dz3, m2[0], l, wbias, dz2);
+    dz_below(S.w3, dz3, m2[0], l, drow ? drow + layer : nullptr, rows, dz2);
     put_rows(S.dz, dz2, col, h, true);
     put_rows(S.hin, h1[0], col, h, valid);
     __syncthreads();
-    put_bias(S, G + L.b2, first);
     hidden_wgrad(S, G + L.w2, l, wave, first);
     __syncthreads();
-    dz_below(S.w2, dz2, m1[0], l, wbias, dz1);
+    dz_below(S.w2, dz2, m1[0], l, drow, rows, dz1);
     put_rows(S.dz, dz1, col, h, true);
 #pragma unroll
     for (int t = 0; t < 8; ++t) S.hin[(8 * h + t) * kLdH + col] = valid ? xb[0][t] : (__bf16)0.f;
     __syncthreads();
-    put_bias(S, G + L.b1, first);
-    const floatx16 acc = row_product(S.dz + col * kLdH + 8 * h, S.hin + min(l & 31, kFeat - 1) * kLdH + 8 * h);
-    if ((l & 31) < kFeat) put_tile(G + L.w1, kFeat, 32 * wave, l & 31, h, acc, first);
+    const int feature = min(l & 31, kFeat - 1);
+    const floatx16 acc = row_product(S.dz + col * kLdH + 8 * h, S.hin + feature * kLdH + 8 * h,
+                                     get_tile(G + L.w1, kFeat, 32 * wave, feature, h, first));
+    if ((l & 31) < kFeat) put_tile(G + L.w1, kFeat, 32 * wave, l & 31, h, acc);
     __syncthreads();
   }
 }
 
-// Gradient = sum of the slabs in order: to grad, or (p != nullptr) straight into an Adam step on p, m, v.
-// The first wave adds the squared errors: loss = sum / n.
-__global__ void __launch_bounds__(256) k_mlp_reduce(const float* slab, int slabs, const double* partial, long n,
-                                                    float* loss, float* grad, float* p, float* m, float* v, float lr,
-                                                    float b1, float b2, float eps, float c1, float c2) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (blockIdx.x == 0 && threadIdx.x < 64) {
+// Weight gradients = sums of the slabs in order (kReduceGrid blocks), bias gradients = sums of dz over the rows, in
+// the order of 256 strided sums and a tree (kBiasGrid blocks of 4 columns): to grad, or (p != nullptr) straight
+// into an Adam step on p, m, v.  The first wave adds the squared errors: loss = sum / n.
+constexpr unsigned kReduceGrid = (unsigned)((MlpLayout::total + 255) / 256);
+constexpr unsigned kBiasGrid = 3 * kHidden / 4 + 1;   // the last block: the output layer's kOut columns
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float* slab, int slabs, const double* partial,
+                                                    const float* dz, const float* dy, long rows, float* loss, float* grad,
+                                                    float* p, float* m, float* v, float lr, float b1, float b2,
+                                                    float eps, float c1, float c2) {
+  __shared__ float sh[4][256];
+  const MlpLayout L;
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid < 64) {
     double s = 0.0;
-    for (int b = threadIdx.x; b < slabs; b += 64) s += partial[b];
+    for (int b = tid; b < slabs; b += 64) s += partial[b];
     for (int k = 32; k > 0; k >>= 1) s += __shfl_xor(s, k);
-    if (threadIdx.x == 0) *loss = (float)(s / (double)n);
+    if (tid == 0) *loss = (float)(s / (double)(rows * kOut));
   }
-  if (i >= (int)MlpLayout::total) return;
+  int i = -1;
   float gi = 0.f;
+  if (blockIdx.x < kReduceGrid) {
+    i = blockIdx.x * 256 + tid;
+    const bool bias = (i >= L.b1 && i < L.w2) || (i >= L.b2 && i < L.w3) || (i >= L.b3 && i < L.w4) || i >= L.b4;
+    if (bias) return;
 #pragma unroll 16
-  for (int b = 0; b < slabs; ++b) gi += slab[(size_t)b * kSlab + i];
+    for (int b = 0; b < slabs; ++b) gi += slab[(size_t)b * kSlab + i];
+  } else {
+    const int g = blockIdx.x - kReduceGrid, layer = g / (kHidden / 4), c0 = 4 * (g % (kHidden / 4));
+    const bool last = layer == 3;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (last) {
+      for (long r = tid; r < rows; r += 256)
+#pragma unroll
+        for (int k = 0; k < kOut; ++k) s[k] += dy[r * kOut + k];
+    } else {
+      const float* d = dz + layer * rows * kHidden + c0 * rows;
+#pragma unroll 16
+      for (long r = tid; r < rows; r += 256) {
+        const float4 q = *reinterpret_cast<const float4*>(d + r * 4);
+        s[0] += q.x; s[1] += q.y; s[2] += q.z; s[3] += q.w;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sh[k][tid] = s[k];
+    __syncthreads();
+    // a wave per column: the tree t + 128, t + 64, ..., t + 1
+    const int c = tid >> 6, l = tid & 63;
+    gi = (sh[c][l] + sh[c][l + 128]) + (sh[c][l + 64] + sh[c][l + 192]);
+    for (int k = 32; k > 0; k >>= 1) gi += __shfl_down(gi, k);
+    if (l != 0 || (last && c >= kOut)) return;
+    i = (int)(layer == 0 ? L.b1 : layer == 1 ? L.b2 : layer == 2 ? L.b3 : L.b4) + (last ? 0 : c0) + c;
+  }
   if (!p) {
     grad[i] = gi;
     return;
@@ -601,27 +630,25 @@ void prepare_mlp() {
 }
 
 static void launch_grad_blocks(const float* W, const float* norm, const float* feat, const float* lab, const int* idx,
-                               long rows, float* slab, double* partial, hipStream_t s) {
+                               long rows, const GradScratch& g, hipStream_t s) {
   hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)grad_slabs(rows)), dim3(64 * kWaves), kGradSmem, s, W, norm, feat, lab,
-                     idx, rows, slab, partial);
+                     idx, rows, grad_span(rows), g.slab, g.partial, g.dz, g.dy);
 }
 
-constexpr unsigned kReduceGrid = (unsigned)((MlpLayout::total + 255) / 256);
-
-void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss, float* slab,
-                     double* partial, hipStream_t s) {
-  launch_grad_blocks(W, nullptr, X, Lab, nullptr, rows, slab, partial, s);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(256), 0, s, slab, (int)grad_slabs(rows), partial,
-                     kOut * rows, loss, grad, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
+void launch_mlp_grad(const float* W, const float* X, const float* Lab, long rows, float* grad, float* loss,
+                     const GradScratch& g, hipStream_t s) {
+  launch_grad_blocks(W, nullptr, X, Lab, nullptr, rows, g, s);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid + kBiasGrid), dim3(256), 0, s, g.slab, (int)grad_slabs(rows),
+                     g.partial, g.dz, g.dy, rows, loss, grad, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
 }
 
 void launch_mlp_train(float* W, const float* norm, const float* feat, const float* lab, const int* idx, long rows,
-                      float* m, float* v, float lr, int t, float* loss, float* slab, double* partial, hipStream_t s) {
+                      float* m, float* v, float lr, int t, float* loss, const GradScratch& g, hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-  launch_grad_blocks(W, norm, feat, lab, idx, rows, slab, partial, s);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(256), 0, s, slab, (int)grad_slabs(rows), partial,
-                     kOut * rows, loss, nullptr, W, m, v, lr, b1, b2, 1e-8f, c1, c2);
+  launch_grad_blocks(W, norm, feat, lab, idx, rows, g, s);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid + kBiasGrid), dim3(256), 0, s, g.slab, (int)grad_slabs(rows),
+                     g.partial, g.dz, g.dy, rows, loss, nullptr, W, m, v, lr, b1, b2, 1e-8f, c1, c2);
 }
 
 // per-block partial sums of (Y - L)^2 in fixed order

@@ -50,7 +50,7 @@ uint16_t to_bf16(float f) {
 }
 
 // Scratch of flash_mlp_grad_noalloc, one copy per GPU for the life of the process: the gradient
-// slabs (the trainer's, so that both entry points sum every gradient in the same order), the
+// slabs (the trainer's, so that both entry points sum every gradient in the same order), the rows' dz, the
 // squared-error sums and a loss slot for callers that want none.
 constexpr long kNaRows = 2048;
 constexpr long kNaSlabs = kNaRows / kGradRows;
@@ -58,8 +58,10 @@ static_assert(kNaRows % kGradRows == 0 && kNaSlabs <= kMaxSlabs, "one slab per b
 constexpr size_t kNaOffPartial = 0;
 constexpr size_t kNaOffLoss = 256;
 constexpr size_t kNaOffSlab = 512;
-constexpr size_t kNaBytes = kNaOffSlab + (size_t)kNaSlabs * kSlab * sizeof(float);
-static_assert(kNaSlabs * sizeof(double) <= kNaOffLoss, "squared-error sums fit their slot");
+constexpr size_t kNaOffDz = kNaOffSlab + (size_t)kNaSlabs * kSlab * sizeof(float);
+constexpr size_t kNaOffDy = kNaOffDz + 3 * (size_t)kNaRows * kHidden * sizeof(float);
+constexpr size_t kNaBytes = kNaOffDy + (size_t)kNaRows * kOut * sizeof(float);
+static_assert(kNaSlabs * sizeof(double) <= kNaOffLoss && kNaOffDz % 16 == 0, "scratch regions");
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
@@ -90,8 +92,8 @@ struct flash_mlp {
   std::vector<void*> own;
   float *W = nullptr, *G = nullptr, *Mo = nullptr, *Vo = nullptr, *norm = nullptr;
   float *X = nullptr, *L = nullptr, *Y = nullptr, *loss = nullptr;   // evaluation chunks, minibatch losses
-  float* slab = nullptr;                       // per-workgroup sums of the parameter gradients
   double* partial = nullptr;
+  GradScratch scratch{};                       // of a gradient of up to max_rows rows
   double* moments = nullptr;
   int adam_t = 0;
   std::vector<float> host_norm;
@@ -145,7 +147,11 @@ flash_status flash_mlp_create(int64_t max_rows, uint64_t seed, void* hip_stream,
     m->loss = dmalloc<float>(1 << 16, m->own);
     m->partial = dmalloc<double>(std::max<long>((3 * R + 255) / 256 + 1, kMaxSlabs), m->own);
     m->moments = dmalloc<double>(2 * (kFeat + kOut), m->own);
-    m->slab = dmalloc<float>(grad_slabs(R) * kSlab, m->own);
+    // (fewer rows never take more slabs than one per kGradRows, rounded up, and one)
+    m->scratch.slab = dmalloc<float>(std::min<long>(R / kGradRows + 2, kMaxSlabs) * kSlab, m->own);
+    m->scratch.partial = m->partial;
+    m->scratch.dz = dmalloc<float>(3 * R * kHidden, m->own);
+    m->scratch.dy = dmalloc<float>(R * kOut, m->own);
     // He-uniform weights (bound sqrt(6 / fan_in)), zero biases
     std::vector<float> w(P, 0.f);
     SplitMix64 rng(seed);
@@ -277,7 +283,7 @@ flash_status flash_mlp_grad(flash_mlp* m, const float* x, const float* target, i
   if (!m || !x || !target || !grad || n <= 0) return fail(FLASH_ERR_INVALID_ARG, "null or empty argument");
   if (n > m->max_rows) return fail(FLASH_ERR_CAPACITY, "n exceeds the network's max_rows");
   try {
-    launch_mlp_grad(m->W, x, target, (long)n, m->G, m->loss, m->slab, m->partial, m->stream);
+    launch_mlp_grad(m->W, x, target, (long)n, m->G, m->loss, m->scratch, m->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(m->stream));
     HIPCHK(hipMemcpy(grad, m->G, MlpLayout::total * sizeof(float), hipMemcpyDeviceToHost));
@@ -299,8 +305,9 @@ flash_status flash_mlp_grad_noalloc(const float* params, const float* x, const f
     unsigned char* base = noalloc_scratch();
     prepare_mlp();
     // the loss goes to the caller's buffer, or to the scratch when none is given
-    launch_mlp_grad(params, x, target, (long)n, grad, loss ? loss : reinterpret_cast<float*>(base + kNaOffLoss),
-                    reinterpret_cast<float*>(base + kNaOffSlab), reinterpret_cast<double*>(base + kNaOffPartial), s);
+    const GradScratch g{reinterpret_cast<float*>(base + kNaOffSlab), reinterpret_cast<double*>(base + kNaOffPartial),
+                        reinterpret_cast<float*>(base + kNaOffDz), reinterpret_cast<float*>(base + kNaOffDy)};
+    launch_mlp_grad(params, x, target, (long)n, grad, loss ? loss : reinterpret_cast<float*>(base + kNaOffLoss), g, s);
     HIPCHK(hipGetLastError());
   } catch (const FlashError& ex) {
     return fail(ex.st, ex.what());
@@ -329,7 +336,7 @@ flash_status flash_mlp_train(flash_mlp* m, const float* feat, const float* lab, 
       HIPCHK(hipMemcpyAsync(idx, perm.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, m->stream));
       for (long q = 0; q < nb; ++q)
         launch_mlp_train(m->W, m->norm, feat, lab, idx + q * batch, batch, m->Mo, m->Vo, lr, ++m->adam_t, m->loss + q,
-                         m->slab, m->partial, m->stream);
+                         m->scratch, m->stream);
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(m->stream));
       HIPCHK(hipMemcpy(lh.data(), m->loss, nb * sizeof(float), hipMemcpyDeviceToHost));
